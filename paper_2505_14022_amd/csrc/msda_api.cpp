@@ -122,6 +122,7 @@ msda::Params base_params(const int64_t* shapes, const int64_t* starts, int64_t S
     p.L = (int)L;
     p.P = (int)P;
     p.K = (int)(L * P);
+    p.inv_P = 1.f / (float)P;
     for (int l = 0; l < msda::kMaxLevels; ++l) {
         p.H[l] = l < L ? (int)shapes[2 * l] : 1;
         p.W[l] = l < L ? (int)shapes[2 * l + 1] : 1;

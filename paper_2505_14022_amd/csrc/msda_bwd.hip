@@ -66,6 +66,7 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
     // after all sums are formed
     __shared__ float s_g[kWaves][ATOMIC ? kAtomicRowFloats : 1];
     __shared__ int4 s_sum_atomic[kWaves][ATOMIC ? kMaxItems : 1];
+    __shared__ int s_q[kWaves][PPW];  // the wave's queries
     int4* const s_sum = ATOMIC ? &s_sum_atomic[0][0] : &s_off[0][0];  // [kWaves][kMaxItems] when used
     load_levels(p, s_lvl);
 
@@ -78,7 +79,9 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
     const rsrc_t vr = make_rsrc(p.value, p.value_bytes);
     const rsrc_t gr = make_rsrc(p.grad_value, p.gv_bytes);
     const T* gout = static_cast<const T*>(p.grad_out);
-    const int q_mine = t.q0 + ps;
+    if (lane < PPW) s_q[wave][lane] = query_at(p, s_lvl, t.q0 + lane);
+    wave_lds_sync();
+    const int q_mine = s_q[wave][ps];
     const bool q_ok = q_mine < p.Lq;
     const size_t gout_row = ((size_t)(t.n * p.Lq + (q_ok ? q_mine : 0)) * p.M + t.m) * p.D;
     // when the query's channels fit one pass of its lanes, its grad_out row is read once here
@@ -105,11 +108,12 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
     const int kb = t.part * kper, ke = kb + kper < K ? kb + kper : K;
     for (int k0 = kb; k0 < ke; k0 += KC) {
         const int kn = ke - k0 < KC ? ke - k0 : KC;
+        const float inv_kn = __builtin_amdgcn_rcpf((float)kn);
         wave_lds_sync();
         for (int j = lane; j < PPW * kn; j += 64) {
-            const int jq = j / kn, jk = j - jq * kn;
+            const int jq = small_div(j, inv_kn), jk = j - jq * kn;
             SampleDesc sd;
-            describe(p, s_lvl, t.n, t.m, t.q0 + jq, k0 + jk, false, sd);
+            describe(p, s_lvl, t.n, t.m, s_q[wave][jq], k0 + jk, false, sd);
             s_off[wave][j] = sd.off;
             s_x[wave][j] = make_float4(sd.a, sd.lh, sd.lw, 0.f);
         }
@@ -262,8 +266,8 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
         // one sample per lane: <g, s> = sum_c w_c G_c, and the location terms are weighted
         // differences of the G_c, scaled by the attention weight and the level size
         for (int j = lane; j < PPW * kn; j += 64) {
-            const int jq = j / kn, jk = j - jq * kn;
-            const int q = t.q0 + jq;
+            const int jq = small_div(j, inv_kn), jk = j - jq * kn;
+            const int q = s_q[wave][jq];
             if (q < p.Lq) {
                 const int4 gi = s_sum[wave * kMaxItems + j];
                 const float G0 = __builtin_bit_cast(float, gi.x), G1 = __builtin_bit_cast(float, gi.y);
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
                     else *gl = make_float2(a * gw, a * gh);
                     s_x[wave][j] = make_float4(a, ga, a * ga, 0.f);
                 } else {
-                    const int l = (k0 + jk) / p.P;
+                    const int l = level_of_sample(p, k0 + jk);
                     const float Wf = (float)s_lvl[kMaxLevels + l], Hf = (float)s_lvl[l];
                     float2* gl = reinterpret_cast<float2*>(p.grad_loc) + smp;
                     if (p.stream_grads) {
@@ -300,8 +304,8 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
             // d loss / d logit_k = a_k (grad_attn_k - sum_i a_i grad_attn_i)
             wave_lds_sync();
             for (int j = lane; j < PPW * kn; j += 64) {
-                const int jq = j / kn, jk = j - jq * kn;
-                const int q = t.q0 + jq;
+                const int jq = small_div(j, inv_kn), jk = j - jq * kn;
+                const int q = s_q[wave][jq];
                 if (q < p.Lq) {
                     float dot = 0.f;
                     for (int i = 0; i < kn; ++i) dot += s_x[wave][jq * kn + i].z;

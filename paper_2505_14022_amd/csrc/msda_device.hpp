@@ -253,7 +253,7 @@ __device__ __forceinline__ float2 group_softmax_stats(float z, int G) {
 // ---------------------------------------------------------------- work decomposition
 
 struct Tile {
-    int n, m, q0;  // slab (n, m) and the first query of this wave
+    int n, m, q0;  // slab (n, m) and the first query (place in the query order, see query_at) of this wave
     int part;      // which of the p.k_split parts of the queries' samples this workgroup takes
 };
 
@@ -276,7 +276,7 @@ __device__ __forceinline__ bool tile_of(const Params& p, int PPW, Tile& t) {
         const int x = (int)(b & 7u), i = (int)(b >> 3);
         slab = i / p.band_cap;
         int k = i - slab * p.band_cap;
-        if (slab >= p.n_batch * p.M || k >= p.band_count[x]) return false;
+        if (slab >= p.n_batch * p.M / p.head_group || k >= p.band_count[x]) return false;
         chunk = -1;
         for (int l = 0; l < p.L; ++l) {
             const int c0 = p.band_c[l][x], n = p.band_c[l][x + 1] - c0;
@@ -292,7 +292,7 @@ __device__ __forceinline__ bool tile_of(const Params& p, int PPW, Tile& t) {
         const int per = (p.chunks + 7) >> 3;
         slab = i / per;
         chunk = (int)(((int64_t)x * p.chunks) >> 3) + (i - slab * per);
-        if (slab >= p.n_batch * p.M || chunk >= (int)(((int64_t)(x + 1) * p.chunks) >> 3)) return false;
+        if (slab >= p.n_batch * p.M / p.head_group || chunk >= (int)(((int64_t)(x + 1) * p.chunks) >> 3)) return false;
     } else {
 #ifndef MSDA_ABLATE_NO_XCD_REMAP
         const uint32_t w = (b & 7u) * (G >> 3) + (b >> 3);
@@ -313,16 +313,35 @@ __device__ __forceinline__ bool tile_of(const Params& p, int PPW, Tile& t) {
         slab = n * p.M + m;
 #endif
     }
-    t.n = slab / p.M;
-    t.m = slab - t.n * p.M;
+    // slabs are taken p.head_group at a time: the heads of one group share cache lines, so the waves of
+    // a workgroup take the same queries of all of them
+    const int groups = p.M / p.head_group;
+    const int waves = p.q_per_block / PPW;  // waves per head
+    const int wave = (int)(threadIdx.x >> 6), hg = wave / waves;
+    t.n = slab / groups;
+    t.m = (slab - t.n * groups) * p.head_group + hg;
     t.part = 0;
     if (p.k_split > 1) {
         // the parts of one query chunk are consecutive work items
         t.part = chunk % p.k_split;
         chunk /= p.k_split;
     }
-    t.q0 = chunk * p.q_per_block + (int)(threadIdx.x >> 6) * PPW;
+    t.q0 = chunk * p.q_per_block + (wave - hg * waves) * PPW;
     return true;
+}
+
+// The query at place i of the query order: the query index, or with p.strip_rows (self-attention over
+// the maps) strips of that many rows, so that consecutive places are a compact patch of the level
+// and the queries of a CU's waves read fewer distinct rows: the fp16 gathers are bound by the vector
+// cache's misses. Read requests to L2 per forward call: Swin-feature shape 33 -> 20 M, DETR-encoder
+// shape 9.4 -> 6.1 M. Places past Lq stay past Lq.
+__device__ __forceinline__ int query_at(const Params& p, const int* s_lvl, int i) {
+    if (!p.strip_rows || i >= p.Lq) return i;
+    int l = 0;
+    for (int j = 1; j < p.L; ++j)
+        if (i >= p.start[j]) l = j;
+    const int st = s_lvl[2 * kMaxLevels + l];
+    return st + strip_pixel(i - st, s_lvl[l], s_lvl[kMaxLevels + l], p.strip_rows);
 }
 
 // The arrangement of tile_of. Query eighths when there are at least half as many queries as value
@@ -359,6 +378,11 @@ inline bool xcd_bands(const Params& p) {
 #endif
 }
 
+// The level of sample k of a query.
+__device__ __forceinline__ int level_of_sample(const Params& p, int k) {
+    return p.K < (1 << 20) ? small_div(k, p.inv_P) : k / p.P;
+}
+
 // Per-sample description computed in phase 1.
 struct SampleDesc {
     int4 off;    // element offsets of the four corner rows (channel 0), or kOOBElem
@@ -376,7 +400,7 @@ __device__ __forceinline__ void describe_at(const Params& p, const int* s_lvl, i
     sd.a = 0.f;
     sd.lh = 0.f;
     sd.lw = 0.f;
-    const int l = k / p.P;
+    const int l = level_of_sample(p, k);
     const int H = s_lvl[l], W = s_lvl[kMaxLevels + l], st = s_lvl[2 * kMaxLevels + l];
     const float Hf = (float)H, Wf = (float)W;
     const float w_im = __builtin_fmaf(xy.x, Wf, -0.5f);
@@ -416,7 +440,7 @@ __device__ __forceinline__ void describe(const Params& p, const int* s_lvl, int 
 // coordinates come first): reference point on the level plus the offset divided by the level size,
 // the division and then the addition each rounded once in fp32.
 __device__ __forceinline__ float2 fused_location(const Params& p, const int* s_lvl, int n, int m, int q, int k) {
-    const int l = k / p.P;
+    const int l = level_of_sample(p, k);
     const int smp = ((n * p.Lq + q) * p.M + m) * p.K + k;
     const float2 o = reinterpret_cast<const float2*>(p.pix_offsets)[smp];
     const float2 r = reinterpret_cast<const float2*>(p.ref)[(n * p.Lq + q) * p.L + l];
@@ -474,25 +498,35 @@ hipError_t launch_lpp(Params p, int lpp, hipStream_t stream) {
     auto go = [&](auto kernel, int ppw) -> hipError_t {
         const int64_t chunks4 = (p.Lq + kWaves * ppw - 1) / (kWaves * ppw);
         const int waves = (int64_t)p.n_batch * p.M * chunks4 < kSmallGrid ? 1 : kWaves;
-        p.q_per_block = waves * ppw;
+        // Strips of rows where the queries are the pixels (as many queries as pixels; if they are in
+        // another order only the speed changes), and two heads per workgroup where two heads' rows of
+        // one pixel are one 128-byte cache line. Forward / backward us before and after, same box:
+        // Swin-feature shape fp16 188 / 853 -> 151 / 811, BEV-temporal fp16 207 / 792 -> 186 / 751,
+        // DETR-encoder fp32 91 / 300 -> 89 / 293 (its 128-byte rows hit the cache more often, and its
+        // loads run at 0.7 of the cache's rate). Strips of 16 rows were 2-5 % slower, of 4 rows 1-15 %
+        // in the backward; workgroups of 8 or 16 waves were slower.
+        p.strip_rows = waves > 1 && xcd_split(p) && xcd_bands(p) && p.S < kStripMaxPixels ? kStripRows : 0;
+        p.head_group = waves > 1 && p.M % 2 == 0 && p.D * (int)sizeof(T) == 64 ? 2 : 1;
+        p.q_per_block = waves * ppw / p.head_group;
         const int qchunks = (p.Lq + p.q_per_block - 1) / p.q_per_block;
         // a grid too small to fill the chip splits each query's samples over up to k_split_max
         // work items, as long as a part keeps kSplitMinSamples samples
         int ks = 1;
         while (2 * ks <= p.k_split_max && 2 * ks * kSplitMinSamples <= p.K &&
-               (int64_t)p.n_batch * p.M * qchunks * waves * 2 * ks <= kSplitWaves)
+               (int64_t)p.n_batch * p.M * qchunks * (p.q_per_block / ppw) * 2 * ks <= kSplitWaves)
             ks *= 2;
         p.k_split = ks;
         p.chunks = qchunks * ks;
-        p.num_blocks = p.n_batch * p.M * p.chunks;
+        const int n_groups = p.n_batch * p.M / p.head_group;
+        p.num_blocks = n_groups * p.chunks;
         if (p.num_blocks == 0) return hipSuccess;
-        const int64_t split_grid = 8 * (int64_t)p.n_batch * p.M * ((p.chunks + 7) / 8);
+        const int64_t split_grid = 8 * (int64_t)n_groups * ((p.chunks + 7) / 8);
         p.xcd_split = xcd_split(p) && split_grid <= INT32_MAX;
         p.xcd_bands = 0;
         int64_t band_grid = 0;
         if (p.xcd_split && ks == 1 && xcd_bands(p)) {
             set_bands(p);
-            band_grid = 8 * (int64_t)p.n_batch * p.M * p.band_cap;
+            band_grid = 8 * (int64_t)n_groups * p.band_cap;
             p.xcd_bands = band_grid <= INT32_MAX;
         }
         const int grid = p.xcd_bands ? (int)band_grid : p.xcd_split ? (int)split_grid : (p.num_blocks + 7) / 8 * 8;

@@ -44,10 +44,36 @@ constexpr int kChunkRecords = 512;   // records folded by one accumulate work it
 // per workgroup and so fewer bin atomics, made the backward 3-14 % slower), and their samples.
 constexpr int kBinBlock = 256;
 constexpr int kCountQueries = 16 * kBinBlock;
+constexpr int kStripRows = 8;        // rows of a strip of the gather kernels' query order
+constexpr int64_t kStripMaxPixels = int64_t(1) << 20;  // maps of this many pixels keep the index order (small_div)
 constexpr int kScanTiles = 256;      // tiles per workgroup in the scan passes (one per thread)
 constexpr int kAtomicMaxSamples = 16384;  // problems this small take the atomic grad_value path
 // Bytes of the static device scratch of msda_backward_noalloc (per GPU, held until the process ends).
 constexpr size_t kStaticScratchBytes = size_t(128) << 20;
+
+// j / d for 0 <= j < 2^20 and 1 <= d, given inv = 1 / d within an ulp or two: the distance of
+// (j + 1/2) / d to the next integer, at least 1 / (2 d), is more than the rounding errors move it.
+// (An integer division by a number known only at run time takes about twenty instructions.)
+__host__ __device__ inline int small_div(int j, float inv) { return (int)(((float)j + 0.5f) * inv); }
+
+// 1 / x, within an ulp on the GPU.
+__host__ __device__ inline float fast_rcp(float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_rcpf(x);
+#else
+    return 1.f / x;
+#endif
+}
+
+// Pixel of a level of less than 2^20 pixels (row-major) at place r of the order that runs over the
+// level in strips of `strip` rows, column by column within a strip; the last strip has the rows that
+// are left.
+__host__ __device__ inline int strip_pixel(int r, int H, int W, int strip) {
+    const int area = strip * W, s = small_div(r, fast_rcp((float)area)), rem = r - s * area, top = s * strip;
+    const int rows = H - top < strip ? H - top : strip;
+    const int col = small_div(rem, fast_rcp((float)rows));
+    return (top + rem - col * rows) * W + col;
+}
 
 // Everything one launch needs, passed by value as the kernel argument.
 struct Params {
@@ -67,8 +93,11 @@ struct Params {
     uint32_t value_bytes;  // size of the value buffer resource
     uint32_t gv_bytes;     // size of the grad_value buffer resource
     int n_batch, S, M, D, Lq, L, P, K;  // K = L*P samples per (query, head)
+    float inv_P;           // 1 / P
     int q_per_block;       // queries of one (n, m) handled by one workgroup
     int chunks;            // work items per slab: ceil(Lq / q_per_block) * k_split
+    int strip_rows;        // query order of the gather kernels: strips of this many rows (0: the query index)
+    int head_group;        // heads that one workgroup of the gather kernels takes together (divides M)
     int k_split;           // bwd_kernel: a query chunk's samples are split over k_split work items
     int k_split_max;       // set by the launcher: the largest k_split it accepts (0 or 1: none)
     int xcd_split;         // forward / bwd_kernel work arrangement (tile_of): 1 query eighths, 0 slab ranges

@@ -1,0 +1,44 @@
+// Host checks of the launch arithmetic that kernels and host code share (csrc/msda_internal.h), by
+// brute force: prints "failures: 0" when every check holds.
+#include <cstdio>
+#include <initializer_list>
+#include <vector>
+
+#include "msda_internal.h"
+
+int main() {
+    int failures = 0;
+    // strip_pixel is a permutation of a level's pixels, and every run of strip * n places that starts at a
+    // strip's column covers n whole columns of the strip
+    for (int H : {1, 2, 7, 8, 9, 15, 16, 23, 100, 1000})
+        for (int W : {1, 2, 5, 8, 33, 1048}) {
+            if ((int64_t)H * W >= msda::kStripMaxPixels) continue;
+            const int strip = msda::kStripRows;
+            std::vector<int> seen(H * W, 0);
+            bool ok = true;
+            for (int r = 0; r < H * W; ++r) {
+                const int px = msda::strip_pixel(r, H, W, strip);
+                ok = ok && px >= 0 && px < H * W && ++seen[px] == 1;
+                const int s = r / (strip * W), top = s * strip, rows = H - top < strip ? H - top : strip;
+                ok = ok && px / W >= top && px / W < top + rows && px % W == (r - top * W) / rows;
+            }
+            if (!ok) {
+                ++failures;
+                std::printf("strip_pixel %d x %d\n", H, W);
+            }
+        }
+    // small_div over its range, with the reciprocal off by up to two units in the last place
+    for (int d : {1, 2, 3, 4, 5, 6, 7, 9, 12, 16, 31, 127, 128, 1000, 4097, 65535, 1048575})
+        for (int ulps = -2; ulps <= 2; ++ulps) {
+            const float inv = (1.f / (float)d) * (1.f + (float)ulps * 5.9604645e-8f);
+            for (int j = 0; j < (1 << 20); j += d < 64 ? 1 : 7)
+                for (int e : {j, j / d * d, j / d * d + d - 1}) {
+                    if (e >= (1 << 20)) continue;
+                    if (msda::small_div(e, inv) != e / d) {
+                        if (failures++ < 10) std::printf("small_div %d / %d\n", e, d);
+                    }
+                }
+        }
+    std::printf("failures: %d\n", failures);
+    return failures != 0;
+}
