@@ -37,8 +37,8 @@
  *
  * State kept between calls (a deviation from a stateless library, for speed): the owner-computes
  * backward (msda_backward and msda_backward_deterministic with a workspace, msda_backward_fused
- * with the owner-computes part of its workspace) runs its grad_value kernels on a second stream,
- * forked from `stream` at the start of the call and joined back into it before the call's last
+ * with the owner-computes part of its workspace), except for small problems, runs its grad_value
+ * kernels on a second stream, forked from `stream` at the start of the call and joined back into it before the call's last
  * work item, so everything enqueued on `stream` afterwards is ordered after all of the call's work
  * (also under stream capture). That stream and its two events belong to the library: one set per
  * device (the device of `stream`), created by the first such call on that device, shared by all

@@ -250,7 +250,16 @@ msda_status_t backward_body(const void* value, const int64_t* shapes, const int6
 #ifdef MSDA_ABLATE_ONE_STREAM
     one_stream = true;
 #endif
-    if (binned && !one_stream) {
+    // a problem binned slab by slab is over before a second stream would pay for its two events
+    bool small = false;
+    if (binned) {
+        msda::Params p = base_params(shapes, starts, S, M, D, Lq, L, P);
+        p.n_batch = (int)(N < nb ? N : nb);
+        p.one_launch = N <= nb;
+        p.deterministic = deterministic ? 1 : 0;
+        small = msda::plan_binned(p) && p.slab_bins;
+    }
+    if (binned && !one_stream && !small) {
         side_lock.lock();
         side = side_stream(stream_device(s));
         if (!side) side_lock.unlock();
@@ -264,6 +273,7 @@ msda_status_t backward_body(const void* value, const int64_t* shapes, const int6
         const int64_t smp0 = pro ? 0 : n0 * Lq * M * L * P;  // staging holds one chunk
         msda::Params p = base_params(shapes, starts, S, M, D, Lq, L, P);
         p.n_batch = (int)cnt;
+        p.one_launch = N <= nb;
         p.deterministic = deterministic ? 1 : 0;
         p.value = static_cast<const char*>(value) + n0 * S * M * D * es;
         p.loc = smp.loc + smp0 * 2;
@@ -297,21 +307,29 @@ msda_status_t backward_body(const void* value, const int64_t* shapes, const int6
             if (!msda::plan_binned(p))
                 return fail(MSDA_ERROR_LAUNCH_FAILED, "internal: binned plan changed between batches");
             msda::bind_workspace(p, workspace);
-            // the workspace's counters are zeroed on `s`, before the grid-wide work starts there
-            if ((e = msda::launch_binned_reset(p, s)) != hipSuccess)
+            // the workspace's counters are zeroed on `s`, before the grid-wide work starts there (a small
+            // problem has one counter, and bwd_kernel zeroes it)
+            if (small) p.reset = p.scan_done;
+            else if ((e = msda::launch_binned_reset(p, s)) != hipSuccess)
                 return fail(MSDA_ERROR_LAUNCH_FAILED, "workspace reset: %s", hipGetErrorString(e));
         }
         // grad_value (binned) on the side stream, forked after everything enqueued on `s` so far
         if (side && ((e = hipEventRecord(side->fork, s)) != hipSuccess ||
                      (e = hipStreamWaitEvent(side->s, side->fork, 0)) != hipSuccess))
             return fail(MSDA_ERROR_LAUNCH_FAILED, "backward fork: %s", hipGetErrorString(e));
+        if (small) {
+            e = msda::launch_backward_grads(p, (msda_dtype_t)dtype, false, s);
+            if (e != hipSuccess) return fail(MSDA_ERROR_LAUNCH_FAILED, "backward launch: %s", hipGetErrorString(e));
+        }
         if (binned) {
             e = msda::launch_backward_value_binned(p, (msda_dtype_t)dtype, side ? side->s : s);
             if (e != hipSuccess)
                 return fail(MSDA_ERROR_LAUNCH_FAILED, "backward grad_value launch: %s", hipGetErrorString(e));
         }
-        e = msda::launch_backward_grads(p, (msda_dtype_t)dtype, !binned, s);
-        if (e != hipSuccess) return fail(MSDA_ERROR_LAUNCH_FAILED, "backward launch: %s", hipGetErrorString(e));
+        if (!small) {
+            e = msda::launch_backward_grads(p, (msda_dtype_t)dtype, !binned, s);
+            if (e != hipSuccess) return fail(MSDA_ERROR_LAUNCH_FAILED, "backward launch: %s", hipGetErrorString(e));
+        }
         if (grads_in_kernel) {
             if (pro->grad_ref &&
                 (e = msda::launch_ref_grad_from_offsets(p, p.grad_loc, pro->grad_ref + n0 * Lq * L * 2, s)) !=
@@ -388,6 +406,7 @@ msda_status_t msda_backward_workspace_size(const int64_t* spatial_shapes, const 
     const int64_t nb = batch_per_launch(S, M, D, Lq, L, P);
     msda::Params p = base_params(spatial_shapes, level_start_index, S, M, D, Lq, L, P);
     p.n_batch = (int)(N < nb ? N : nb);
+    p.one_launch = N <= nb;
     p.deterministic = det ? 1 : 0;
     if (mode == MSDA_WORKSPACE_PREFERRED && msda::prefer_atomic(p)) return ok();
     if (msda::plan_binned(p)) *bytes = msda::binned_workspace_bytes(p);

@@ -69,6 +69,7 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
     __shared__ int s_q[kWaves][PPW];  // the wave's queries
     int4* const s_sum = ATOMIC ? &s_sum_atomic[0][0] : &s_off[0][0];  // [kWaves][kMaxItems] when used
     load_levels(p, s_lvl);
+    if (p.reset && blockIdx.x == 0 && threadIdx.x == 0) *p.reset = 0;
 
     Tile t;
     if (!tile_of(p, PPW, t)) return;

@@ -20,6 +20,7 @@
 //               sample (own bin plus the left / up / up-left neighbours' straddling classes)
 //               and stores the tile's grad_value rows; items of a split tile add theirs with
 //               atomics into rows that were zeroed before.
+#include <algorithm>
 #include <atomic>
 
 #include "msda_device.hpp"
@@ -31,6 +32,7 @@ namespace {
 // first bin of the level within a slab
 constexpr int kGeo = 9;
 constexpr int kAccWaves = 4;
+constexpr int kTileEdge = 8;  // pixels of a tile's edge where D % 4 == 0
 
 __device__ __forceinline__ void load_geo(const Params& p, int* s) {
     if (threadIdx.x < kMaxLevels) {
@@ -250,7 +252,7 @@ __device__ __forceinline__ void tile_totals(const Params& p, const int* g, int t
 #pragma unroll
     for (int i = 0; i < kKeyedBins; ++i) own += c[i];
     const int vis = own + e[0] + e[1] + e[2] + e[3] + e[4];
-    items = vis > 0 ? (vis + kChunkRecords - 1) / kChunkRecords : 1;
+    items = vis > 0 ? (vis + p.item_records - 1) / p.item_records : 1;
 }
 
 // Exclusive block scan of two sequences (256 threads); returns the block totals.
@@ -395,8 +397,8 @@ __device__ __forceinline__ void prep_tile(const Params& p, const int* s_geo, int
     const int nvis = na + nb + nc + nd;
     for (int c = lane; c < nit && first + c < p.max_items; c += 64) {
         int4* d = reinterpret_cast<int4*>(p.item_desc) + (size_t)(first + c) * 4;
-        const int beg = c * kChunkRecords;
-        d[0] = make_int4(beg, min(beg + kChunkRecords, nvis), nit > 1, l);
+        const int beg = c * p.item_records;
+        d[0] = make_int4(beg, min(beg + p.item_records, nvis), nit > 1, l);
         d[1] = make_int4(n, m, h_org, w_org);
         d[2] = make_int4(a0, na, b0, nb);
         d[3] = make_int4(c0, nc, d0, 0);
@@ -515,6 +517,161 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(Params p) {
     constexpr int kPrepWaves = kBinBlock / 64;
     for (int t = blockIdx.x * kPrepWaves + (threadIdx.x >> 6); t < p.n_tiles; t += gridDim.x * kPrepWaves)
         prep_tile(p, s_geo, t, threadIdx.x & 63);
+}
+
+// ---------------------------------------------------------------- 1-3 in one launch, for few samples
+
+// Steps 1 to 3 for one (slab, level) per workgroup: its samples are held in registers, ranked per bin
+// by LDS counters, and written to the level's own part of the records, so there are no counts in
+// memory, no scans over workgroups and no atomics but one per workgroup for its work items. It
+// takes 20-30 us, of which the chain of its phases on one CU is most (5376 to 9000 samples per
+// level: 20 and 31 us, against 45-55 us of kernels and five launches for the passes above).
+constexpr int kSlabThreads = 1024;
+constexpr int kSlabSamples = 16 * kSlabThreads;  // samples of a (slab, level) that one workgroup bins
+template <int HELD>  // samples of a thread, held in registers
+__global__ __launch_bounds__(kSlabThreads) void bin_slab_kernel(Params p) {
+    extern __shared__ int hist[];  // bins of this level, and their end
+    __shared__ int s_geo[kGeo * kMaxLevels];
+    __shared__ int s_wave[2][kSlabThreads / 64];
+    __shared__ int s_item0;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int slab = blockIdx.x / p.L, l = blockIdx.x - slab * p.L;
+    const int n = slab / p.M, m = slab - n * p.M;
+    const float2* loc = reinterpret_cast<const float2*>(p.loc);
+    const int total = p.Lq * p.P;
+    // the thread's samples: place r * kSlabThreads + tid in the level's query-major order
+    float2 xy[HELD];
+    float a[HELD];
+    auto pair_of = [&](int q) { return (n * p.Lq + q) * p.M + m; };
+#pragma unroll
+    for (int r = 0; r < HELD; ++r) {
+        const int j = r * kSlabThreads + tid;
+        xy[r] = make_float2(-2.f, -2.f);  // off the map
+        a[r] = 0.f;
+        if (j < total) {
+            const int q = small_div(j, p.inv_P);
+            const int smp = pair_of(q) * p.K + l * p.P + (j - q * p.P);
+            xy[r] = loc[smp];
+            a[r] = p.attn[smp];
+        }
+    }
+    load_geo(p, s_geo);
+    const int H = s_geo[l], W = s_geo[kMaxLevels + l], B = s_geo[7 * kMaxLevels + l], txn = s_geo[4 * kMaxLevels + l];
+    const int bin0 = s_geo[8 * kMaxLevels + l];
+    const int tiles = (l + 1 < p.L ? s_geo[5 * kMaxLevels + l + 1] : p.tiles_per_slab) - s_geo[5 * kMaxLevels + l];
+    const int bins = tiles * B;
+    for (int i = tid; i <= bins; i += kSlabThreads) hist[i] = 0;
+    __syncthreads();
+    // bin and rank of each sample, and its coordinates on the map
+    static_assert(kHistMax <= 1 << 14 && kSlabSamples <= 1 << 16, "bin and rank in one word");
+    int place[HELD];
+#pragma unroll
+    for (int r = 0; r < HELD; ++r) {
+        float h_im, w_im;
+        const int b = sample_bin(s_geo, l, xy[r], &h_im, &w_im);
+        place[r] = -1;
+        if (b >= 0) place[r] = (b - bin0) << 16 | atomicAdd(&hist[b - bin0], 1);
+        xy[r] = make_float2(h_im, w_im);
+    }
+    __syncthreads();
+    // a contiguous run of tiles per thread: its samples and work items, scanned over the workgroup
+    const int per = (tiles + kSlabThreads - 1) / kSlabThreads;
+    const int t0 = min(tid * per, tiles), t1 = min(t0 + per, tiles);
+    auto count = [&](int t, int c) { return hist[t * B + c]; };
+    int own = 0, items = 0;
+    for (int t = t0; t < t1; ++t) {
+        const int ty = t / txn, tx = t - ty * txn;
+        int mine = 0;
+        for (int c = 0; c < B; ++c) mine += count(t, c);
+        int vis = mine;
+        if (tx > 0) vis += count(t - 1, B - 3) + count(t - 1, B - 2);
+        if (ty > 0) vis += count(t - txn, B - 2) + count(t - txn, B - 1);
+        if (tx > 0 && ty > 0) vis += count(t - txn - 1, B - 2);
+        own += mine;
+        items += vis > 0 ? (vis + p.item_records - 1) / p.item_records : 1;
+    }
+    int own_to = own, items_to = items;  // inclusive over the wave
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(own_to, o, 64), y = __shfl_up(items_to, o, 64);
+        if (lane >= o) {
+            own_to += x;
+            items_to += y;
+        }
+    }
+    if (lane == 63) {
+        s_wave[0][wave] = own_to;
+        s_wave[1][wave] = items_to;
+    }
+    __syncthreads();
+    int own_from = own_to - own, item = items_to - items, all_items = 0;
+    for (int w = 0; w < kSlabThreads / 64; ++w) {
+        if (w < wave) {
+            own_from += s_wave[0][w];
+            item += s_wave[1][w];
+        }
+        all_items += s_wave[1][w];
+    }
+    if (tid == 0) s_item0 = atomicAdd(p.scan_done, all_items);
+    // counts -> offsets within the level
+    for (int t = t0; t < t1; ++t)
+        for (int c = 0; c < B; ++c) {
+            const int k = hist[t * B + c];
+            hist[t * B + c] = own_from;
+            own_from += k;
+        }
+    if (tid == kSlabThreads - 1) hist[bins] = own_from;
+    __syncthreads();
+    const int rec0 = slab * p.Lq * p.K + l * total;  // the level's part of the records
+    int4* records = reinterpret_cast<int4*>(p.records) + rec0;
+#pragma unroll
+    for (int r = 0; r < HELD; ++r)
+        if (place[r] >= 0)
+            records[hist[place[r] >> 16] + (place[r] & 0xffff)] =
+                make_int4(pair_of(small_div(r * kSlabThreads + tid, p.inv_P)) * p.D, __builtin_bit_cast(int, a[r]),
+                          __builtin_bit_cast(int, xy[r].x), __builtin_bit_cast(int, xy[r].y));
+    item += s_item0;
+    auto range = [&](int t, int c, int k, int& first) {  // bins [c, c + k) of tile t
+        first = hist[t * B + c];
+        return hist[t * B + c + k] - first;
+    };
+    struct Visible {
+        int a0, na, b0, nb, c0, nc, d0, nd;
+    };
+    auto visible = [&](int t) {
+        const int ty = t / txn, tx = t - ty * txn;
+        Visible v = {};
+        v.na = range(t, 0, B, v.a0);
+        if (tx > 0) v.nb = range(t - 1, B - 3, 2, v.b0);
+        if (ty > 0) v.nc = range(t - txn, B - 2, 2, v.c0);
+        if (tx > 0 && ty > 0) v.nd = range(t - txn - 1, B - 2, 1, v.d0);
+        return v;
+    };
+    for (int t = t0; t < t1; ++t) {
+        const int ty = t / txn, tx = t - ty * txn;
+        const Visible v = visible(t);
+        const int nvis = v.na + v.nb + v.nc + v.nd;
+        const int nit = nvis > 0 ? (nvis + p.item_records - 1) / p.item_records : 1;
+        for (int c = 0; c < nit; ++c, ++item) {
+            if (item >= p.max_items) break;
+            int4* d = reinterpret_cast<int4*>(p.item_desc) + (size_t)item * 4;
+            const int beg = c * p.item_records;
+            d[0] = make_int4(beg, min(beg + p.item_records, nvis), nit > 1, l);
+            d[1] = make_int4(n, m, ty * kTileEdge, tx * kTileEdge);
+            d[2] = make_int4(rec0 + v.a0, v.na, rec0 + v.b0, v.nb);
+            d[3] = make_int4(rec0 + v.c0, v.nc, rec0 + v.d0, 0);
+        }
+    }
+    // rows of tiles that several work items add into start at zero: a pixel per lane
+    for (int t = wave; t < tiles; t += kSlabThreads / 64) {
+        const Visible v = visible(t);
+        if (v.na + v.nb + v.nc + v.nd <= p.item_records) continue;
+        const int ty = t / txn, tx = t - ty * txn;
+        const int h = ty * kTileEdge + lane / kTileEdge, w = tx * kTileEdge + lane % kTileEdge;
+        if (h >= H || w >= W) continue;
+        float4* row = reinterpret_cast<float4*>(
+            p.grad_value + ((size_t)(n * p.S + s_geo[6 * kMaxLevels + l] + h * W + w) * p.M + m) * p.D);
+        for (int c = 0; c < p.D / 4; ++c) row[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
 }
 
 // ---------------------------------------------------------------- 4. fold
@@ -681,7 +838,7 @@ __global__ __launch_bounds__(256) void fold_kernel(Params p, int tile_floats) {
 
 // ---------------------------------------------------------------- 4. fold by runs (D % 4 == 0)
 
-constexpr int kRunEdge = 8;                               // tiles of this fold are at most 8 x 8 pixels
+constexpr int kRunEdge = kTileEdge;                       // tiles of this fold are at most 8 x 8 pixels
 constexpr int kRunPix = kRunEdge * kRunEdge;
 // key of a record: the tile position of its top-left corner (rows and columns -1 .. 7), one key
 // row per 16 keys so that keys ascend in raster order and decode with shifts
@@ -838,15 +995,19 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     // (2-4 us off the backward against dealing items x, x + 8, ...). Each counter has a 256-byte line of its
     // own: all waves taking items from one counter (or from counters sharing a line) serialize on
     // it, which cost the fold a quarter of its time. A wave whose queue has drained helps the others.
-    int total = p.tile_chunks[p.n_tiles];
-    total = total < 0 ? 0 : (total > p.max_items ? p.max_items : total);
-    int owner = blockIdx.x & (kQueues - 1), visited = 0;
-    auto qbase = [&](int q) { return (int)(((int64_t)total * q) / kQueues); };
-    auto owned = [&](int q) { return qbase(q + 1) - qbase(q); };
+    int total = p.slab_bins ? *p.scan_done : p.tile_chunks[p.n_tiles];
+    total = (total < 0 ? 0 : (total > p.max_items ? p.max_items : total)) * p.ch_blocks;
+    // With p.slab_bins there are a few items per wave at most, and the waves take every nwaves-th one: a
+    // queue's atomics, and the visits to the drained queues at the end, would take longer than the sums.
+    const bool fixed = p.slab_bins != 0;
+    const int nwaves = gridDim.x * kAccWaves;
+    int owner = fixed ? 0 : blockIdx.x & (kQueues - 1), visited = fixed ? kQueues - 1 : 0;
+    auto qbase = [&](int q) { return fixed ? 0 : (int)(((int64_t)total * q) / kQueues); };
+    auto owned = [&](int q) { return fixed ? total : qbase(q + 1) - qbase(q); };
     auto item_at = [&](int q, int s) { return qbase(q) + s; };
     auto counter = [&](int q) { return p.queue + q * kQueueStride; };
-    // descriptor of work item `it`: lanes 0..15 hold its 16 words
-    auto load_desc = [&](int it) { return lane < 16 ? p.item_desc[(size_t)it * 16 + lane] : 0; };
+    // descriptor of work item `it` (its block of channels is it % p.ch_blocks): lanes 0..15 hold its 16 words
+    auto load_desc = [&](int it) { return lane < 16 ? p.item_desc[(size_t)(it / p.ch_blocks) * 16 + lane] : 0; };
     // the item's visible records, kRecPerLane per lane (all loads in flight together); rows past
     // the item's end are marked with x = -1
     auto load_records = [&](int dv, int4 (&rc)[kRecPerLane]) {
@@ -868,8 +1029,8 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
             rc[i] = idx >= 0 && idx < p.n_samples ? records[idx] : make_int4(-1, 0, 0, 0);
         }
     };
-    int taken = 0;
-    if (lane == 0) taken = atomicAdd(counter(owner), 1);
+    int taken = blockIdx.x * kAccWaves + wave;
+    if (!fixed && lane == 0) taken = atomicAdd(counter(owner), 1);
     int pf_item = -1, pf_dv = 0;  // the next item of this queue and its prefetched descriptor
     for (;;) {
         const int slot = __builtin_amdgcn_readfirstlane(taken);
@@ -887,7 +1048,8 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         }
         const int item = item_at(owner, slot);
         // the next slot is taken now; it is needed only when this item is done
-        if (lane == 0) taken = atomicAdd(counter(owner), 1);
+        if (fixed) taken = slot + nwaves;
+        else if (lane == 0) taken = atomicAdd(counter(owner), 1);
         const int dv = item == pf_item ? pf_dv : load_desc(item);
         int4 rc[kRecPerLane];
         load_records(dv, rc);
@@ -1038,7 +1200,10 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         const int lo = (C * grp) / kGroups, hi = (C * (grp + 1)) / kGroups;
         const int span = (C + kGroups - 1) / kGroups;
         const int key_lo = !by_units && hi > lo ? skey[lo] : 0;  // key of the slice's first record
-        for (int ch0 = 0; ch0 < D; ch0 += 4 * kPixQ) {
+        // every channel, or with p.ch_blocks > 1 the item's block of them
+        const int ch_first = p.ch_blocks > 1 ? item % p.ch_blocks * (4 * kPixQ) : 0;
+        const int ch_end = p.ch_blocks > 1 ? min(ch_first + 4 * kPixQ, D) : D;
+        for (int ch0 = ch_first; ch0 < ch_end; ch0 += 4 * kPixQ) {
             const int ch = ch0 + 4 * kQPL * sub;  // the lane's first channel
 #pragma unroll
             for (int it = 0; it < kRunPix * kPixQ / 64; ++it) acc[lane + 64 * it] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1258,6 +1423,33 @@ bool prefer_atomic(const Params& p) {
     return samples <= kAtomicMaxSamples;
 }
 
+namespace {
+// Whether one workgroup per (slab, level) bins the problem (bin_slab_kernel): where the samples of a
+// level fit its registers, and up to 2 M samples, beyond which the many-workgroup passes, beside
+// bwd_kernel on the second stream, are as fast. Backward us, those passes against this, D = 32,
+// samples per level x slabs x levels: 4000 x 16 x 4 122 / 55, 8000 x 64 x 4 187 / 159,
+// 4000 x 128 x 4 216 / 184, 16000 x 64 x 2 242 / 240, 16000 x 64 x 4 243 / 263.
+constexpr int64_t kSlabMaxSamples = int64_t(1) << 21;
+bool slab_bins_apply(const Params& p) {
+    return p.one_launch && !p.deterministic && (int64_t)p.Lq * p.P <= kSlabSamples &&
+           (int64_t)p.n_batch * p.Lq * p.M * p.K <= kSlabMaxSamples;
+}
+
+// Work items of a problem binned by bin_slab_kernel: the blocks of 32 channels are items of their own,
+// and a tile is cut into as few records per item (at least 64) as leaves every item a wave of the
+// fold's resident grid: an item's latency, not the sums, is what such a fold takes (64 thousand
+// samples of 64 channels: 42 us with items of 512 records and all channels, 17 us so).
+constexpr int64_t kResidentWaves = 2048;
+void pick_small_items(Params& p) {
+    const int64_t records = (int64_t)p.n_batch * p.Lq * p.M * p.K * 5 / 4;
+    const int64_t tiles = (int64_t)p.n_batch * p.M * p.tiles_per_slab;
+    p.ch_blocks = (p.D + 4 * kPixQ - 1) / (4 * kPixQ);
+    int r = 64;
+    while (r < kChunkRecords && (tiles + records / r) * p.ch_blocks > kResidentWaves) r *= 2;
+    p.item_records = r;
+}
+}  // namespace
+
 bool plan_binned(Params& p) {
     const bool runs = p.D % 4 == 0;  // the run fold: any D, 8 x 8 tiles, 32 channels at a time
     if ((!runs && p.D > kBinnedMaxD) || p.Lq == 0 || p.K > kCountQueries) return false;
@@ -1359,7 +1551,11 @@ bool plan_binned(Params& p) {
     const int64_t n_tiles = n_slabs * base;
     const int64_t n_bins = n_slabs * bbase;
     const int64_t n_samples = (int64_t)p.n_batch * p.Lq * p.M * p.K;
-    const int64_t max_items = 2 * n_tiles + 4 * n_samples / kChunkRecords + 1;
+    p.item_records = kChunkRecords;
+    p.ch_blocks = 1;
+    p.slab_bins = runs && slab_bins_apply(p);
+    if (p.slab_bins) pick_small_items(p);
+    const int64_t max_items = 2 * n_tiles + 4 * n_samples / p.item_records + 1;
     if (n_bins + 1 > kMaxIndex || max_items > kMaxIndex || n_samples > kMaxIndex) return false;
     p.n_bins = (int)n_bins;
     p.n_slabs = (int)n_slabs;
@@ -1462,11 +1658,44 @@ hipError_t launch_binned_reset(const Params& p, hipStream_t stream) {
     return launch_zero(reinterpret_cast<float*>(p.counts), (int64_t)zeroed_ints(p), stream);
 }
 
+namespace {
+hipError_t launch_fold_runs(const Params& p, msda_dtype_t dtype, hipStream_t stream) {
+    const int grid = queue_grid(stream);  // the waves take work items from the queue
+    if (grid <= 0) return hipErrorInvalidConfiguration;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, p); };
+    if (p.deterministic) {
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, true>);
+        else go(fold_runs_kernel<float, true>);
+    } else {
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false>);
+        else go(fold_runs_kernel<float, false>);
+    }
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_backward_value_binned(const Params& p0, msda_dtype_t dtype, hipStream_t stream) {
     Params p = p0;
     hipError_t e = hipSuccess;
     p.q_per_block = kCountQueries / p.K > 0 ? kCountQueries / p.K : 1;
     p.chunks = (p.Lq + p.q_per_block - 1) / p.q_per_block;
+    if (p.slab_bins) {
+        int most = 0;
+        for (int l = 0; l < p.L; ++l) {
+            const int tiles = (l + 1 < p.L ? p.tile_base[l + 1] : p.tiles_per_slab) - p.tile_base[l];
+            most = std::max(most, tiles * p.tile_bins[l] + 1);
+        }
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(p.n_slabs * p.L), dim3(kSlabThreads), most * sizeof(int), stream, p);
+        };
+        const int held = (p.Lq * p.P + kSlabThreads - 1) / kSlabThreads;
+        if (held <= 2) go(bin_slab_kernel<2>);
+        else if (held <= 4) go(bin_slab_kernel<4>);
+        else if (held <= 8) go(bin_slab_kernel<8>);
+        else go(bin_slab_kernel<16>);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return launch_fold_runs(p, dtype, stream);
+    }
     const int bin_blocks = p.n_slabs * p.chunks;
     const size_t hist_lds = (size_t)p.bins_per_slab * sizeof(int);
     const bool det = p.deterministic != 0;
@@ -1491,20 +1720,8 @@ hipError_t launch_backward_value_binned(const Params& p0, msda_dtype_t dtype, hi
     else hipLaunchKernelGGL(bin_scatter_kernel<false>, scatter_grid, dim3(kBinBlock), hist_lds, stream, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (p.D % 4 == 0) {
-        const int grid = queue_grid(stream);  // the waves take work items from the queue
-        if (grid <= 0) return hipErrorInvalidConfiguration;
-        if (det) {
-            if (dtype == MSDA_F16)
-                hipLaunchKernelGGL((fold_runs_kernel<_Float16, true>), dim3(grid), dim3(256), 0, stream, p);
-            else
-                hipLaunchKernelGGL((fold_runs_kernel<float, true>), dim3(grid), dim3(256), 0, stream, p);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)p.n_tiles), dim3(256), 0, stream, p);
-        } else if (dtype == MSDA_F16) {
-            hipLaunchKernelGGL((fold_runs_kernel<_Float16, false>), dim3(grid), dim3(256), 0, stream, p);
-        } else {
-            hipLaunchKernelGGL((fold_runs_kernel<float, false>), dim3(grid), dim3(256), 0, stream, p);
-        }
+        if ((e = launch_fold_runs(p, dtype, stream)) != hipSuccess || !det) return e;
+        hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)p.n_tiles), dim3(256), 0, stream, p);
         return hipGetLastError();
     }
     int tile_floats = 0;

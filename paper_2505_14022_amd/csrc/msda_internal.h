@@ -88,6 +88,7 @@ struct Params {
     float* grad_value;     // [n_batch, S, M, D] fp32                        (backward)
     float* grad_loc;       // [n_batch, Lq, M, L, P, 2]                      (backward)
     float* grad_attn;      // [n_batch, Lq, M, L, P]                         (backward)
+    int* reset;            // backward: a counter that bwd_kernel zeroes for the kernels after it (or null)
     int prologue_grads;    // backward: grad_loc / grad_attn hold grad_offsets / grad_logits instead
     int stream_grads;      // backward: grad_loc / grad_attn are read by no later kernel of the call
     uint32_t value_bytes;  // size of the value buffer resource
@@ -124,12 +125,17 @@ struct Params {
     int n_slabs;                // n_batch * M
     int n_tiles;                // n_slabs * tiles_per_slab
     int n_samples;              // n_batch * Lq * M * K
+    int one_launch;             // the whole batch is in this launch
+    int slab_bins;              // binning in one launch, a workgroup per (slab, level)
+    int item_records;           // visible records of a tile per work item
+    int ch_blocks;              // work items per descriptor: blocks of 32 channels (1: an item takes all of them)
     int max_items;              // capacity of `items`
     int scan_blocks;            // ceil(n_tiles / kScanTiles)
     int deterministic;          // grad_value summed in an order fixed by the inputs (bitwise reproducible)
     int* counts;                // [n_bins]            samples per bin (tile, class)
     int* queue;                 // [8 * 64]            fold work queue counters, 256 B apart (zeroed with counts)
-    int* scan_done;             // [1]                 workgroups of the scan's first pass done (zeroed with counts)
+    int* scan_done;             // [1]                 workgroups of the scan's first pass done, or with slab_bins
+                                //                     the number of work items (zeroed with counts)
     int* item_desc;             // [max_items * 16]    fold work item descriptors
     int* offsets;               // [n_bins + 1]        exclusive prefix of counts
     int* cursor;                // [n_bins]            fill position per bin

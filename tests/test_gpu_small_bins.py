@@ -1,0 +1,42 @@
+"""The one-launch binning of small problems (a workgroup per batch item, head and level) at the sizes where it can
+go wrong: sample counts around the thread count and at the largest that the path takes (and one more), one-pixel
+and one-tile levels, many levels, channel counts that are no multiple of its blocks, samples all in one cell or
+all off the map. Tolerances are those of the parity tests."""
+import numpy as np
+import pytest
+
+from paper_2505_14022_amd import workloads
+from gpu_util import check_parity, require_gpu
+
+CASES = [
+    # N, M, D, levels, P, Lq, dtype
+    (2, 3, 36, ((5, 9), (3, 2)), 1, 1023, "f32"),
+    (1, 2, 64, ((17, 8), (8, 17), (1, 1)), 1, 1024, "f16"),
+    (1, 2, 100, ((9, 9),), 1, 1025, "f32"),
+    (1, 1, 32, ((40, 33), (8, 8), (1, 3)), 4, 4096, "f32"),     # 16384 samples per level
+    (1, 1, 32, ((40, 33), (8, 8), (1, 3)), 5, 3277, "f32"),     # 16385: the many-workgroup passes
+    (1, 1, 4, tuple((k + 1, 16 - k) for k in range(16)), 2, 700, "f32"),
+    (3, 5, 48, ((31, 23), (16, 12), (8, 6)), 3, 999, "f16"),
+    (1, 1, 32, ((120, 200),), 4, 4000, "f32"),                  # 375 tiles, few samples each
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"D{c[2]}_L{len(c[3])}_P{c[4]}_Lq{c[5]}_{c[6]}")
+def test_small_bins(case):
+    require_gpu()
+    N, M, D, levels, P, Lq, dtype = case
+    check_parity(workloads.random_case(N, M, D, levels, P, Lq, dtype=dtype, seed=D + Lq), workspace="owner")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["one_cell", "off_map"])
+def test_small_bins_degenerate(where):
+    require_gpu()
+    inp = workloads.random_case(1, 2, 32, ((24, 24), (12, 12)), 4, 1500, seed=9)
+    if where == "one_cell":  # every sample of a level in the cell that four tiles share
+        inp.loc[..., 0, :, :] = np.float32(8.25 / 24)
+        inp.loc[..., 1, :, :] = np.float32(8.25 / 12)
+    else:
+        inp.loc[...] = np.float32(-0.5)
+    check_parity(inp, workspace="owner")
