@@ -6,6 +6,7 @@ every step of the computation runs in the library's HIP kernels. There is no fal
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional, Sequence, Tuple
@@ -101,6 +102,8 @@ def release():
 
 def _host_tables(spatial_shapes, level_start_index) -> Tuple[np.ndarray, np.ndarray]:
     def to_np(x):
+        if type(x) is np.ndarray and x.dtype == np.int64 and x.flags.c_contiguous:
+            return x
         if hasattr(x, "detach"):
             x = x.detach().cpu().numpy()
         return np.ascontiguousarray(np.asarray(x), dtype=np.int64)
@@ -108,8 +111,11 @@ def _host_tables(spatial_shapes, level_start_index) -> Tuple[np.ndarray, np.ndar
     return to_np(spatial_shapes).reshape(-1), to_np(level_start_index).reshape(-1)
 
 
+_I64P = ctypes.POINTER(ctypes.c_int64)
+
+
 def _iptr(a: np.ndarray):
-    return a.ctypes.data_as(ctypes.POINTER(ctypes.c_int64))
+    return ctypes.cast(a.__array_interface__["data"][0], _I64P) if a.size else a.ctypes.data_as(_I64P)
 
 
 def _dptr(t) -> Optional[int]:
@@ -130,6 +136,9 @@ def _stream(stream) -> Optional[int]:
     return int(getattr(stream, "cuda_stream", stream))
 
 
+_NO_CONTEXT = contextlib.nullcontext()
+
+
 def _on(stream):
     """A context under which torch allocates memory for use on `stream` (torch's current stream when
     it is None). Outputs and workspaces the binding allocates are used by the kernels enqueued on
@@ -138,7 +147,7 @@ def _on(stream):
     import torch
 
     if stream is None:
-        return torch.cuda.stream(torch.cuda.current_stream())
+        return _NO_CONTEXT  # torch allocates under its current stream anyway (entering it anew costs 7 us)
     if isinstance(stream, torch.cuda.Stream):
         return torch.cuda.stream(stream)
     return torch.cuda.stream(torch.cuda.ExternalStream(_stream(stream)))
