@@ -866,16 +866,16 @@ template <typename T, int VEC>
 struct QuadBuf;
 template <>
 struct QuadBuf<float, 4> {
-    static __device__ __forceinline__ float4 load(rsrc_t r, uint32_t off_elems) {
-        auto x = __builtin_amdgcn_raw_buffer_load_b128(r, off_elems << 2, 0, 0);
+    static __device__ __forceinline__ float4 load(rsrc_t r, uint32_t off_elems, int more) {
+        auto x = __builtin_amdgcn_raw_buffer_load_b128(r, (off_elems << 2) + (more << 2), 0, 0);
         const uint32_t u0 = x[0], u1 = x[1], u2 = x[2], u3 = x[3];
         return make_float4(as_float(u0), as_float(u1), as_float(u2), as_float(u3));
     }
 };
 template <>
 struct QuadBuf<_Float16, 4> {
-    static __device__ __forceinline__ float4 load(rsrc_t r, uint32_t off_elems) {
-        auto x = __builtin_amdgcn_raw_buffer_load_b64(r, off_elems << 1, 0, 0);
+    static __device__ __forceinline__ float4 load(rsrc_t r, uint32_t off_elems, int more) {
+        auto x = __builtin_amdgcn_raw_buffer_load_b64(r, (off_elems << 1) + (more << 1), 0, 0);
         const uint32_t u0 = x[0], u1 = x[1];
         float4 f;
         unpack_h2(u0, f.x, f.y);
@@ -975,7 +975,7 @@ template <typename T, bool DET>
 __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     __shared__ int s_geo[kGeo * kMaxLevels];
     __shared__ int s_start[kAccWaves][kRunKeys + 1];
-    __shared__ int4 s_rec[kAccWaves][kChunkRecords];        // sorted records: {grad_out row, a, lh, lw}
+    __shared__ int4 s_rec[kAccWaves][kChunkRecords + 1];    // sorted records {grad_out row, a, lh, lw}, and a record of nothing
     __shared__ int s_key[kAccWaves][kChunkRecords];         // their keys, or the work units (step 3)
     __shared__ float4 s_acc[kAccWaves][kRunPix * kPixQ];    // 32 channels of the tile
     load_geo(p, s_geo);
@@ -984,6 +984,8 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     int4* srec = s_rec[wave];
     int* skey = s_key[wave];
     float4* acc = s_acc[wave];
+    // places past a unit's or a slice's end read this record: no weight, and a row past grad_out's end
+    if (lane == 0) srec[kChunkRecords] = make_int4((int)kOOBElem, 0, 0, 0);
     const int D = p.D;
     const rsrc_t gr = make_rsrc(p.grad_out, (uint32_t)((size_t)p.n_batch * p.Lq * p.M * D * sizeof(T)));
     const int sub = lane % kLPR, grp = lane / kLPR;  // lane within its record stream, stream
@@ -1204,7 +1206,14 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         const int ch_first = p.ch_blocks > 1 ? item % p.ch_blocks * (4 * kPixQ) : 0;
         const int ch_end = p.ch_blocks > 1 ? min(ch_first + 4 * kPixQ, D) : D;
         for (int ch0 = ch_first; ch0 < ch_end; ch0 += 4 * kPixQ) {
-            const int ch = ch0 + 4 * kQPL * sub;  // the lane's first channel
+            // the lane's first channel, or past the end of every row; channels past D in its other float4s may
+            // read the next row's, and their sums are never stored
+            const int ch = ch0 + 4 * kQPL * sub < D ? ch0 + 4 * kQPL * sub : (int)kOOBElem;
+            auto load_row = [&](float4 (&x)[kQPL], int row) {
+                const uint32_t off = (uint32_t)(row + ch);
+#pragma unroll
+                for (int j = 0; j < kQPL; ++j) x[j] = QuadBuf<T, 4>::load(gr, off, 4 * j);
+            };
 #pragma unroll
             for (int it = 0; it < kRunPix * kPixQ / 64; ++it) acc[lane + 64 * it] = make_float4(0.f, 0.f, 0.f, 0.f);
             wave_lds_sync();
@@ -1216,23 +1225,16 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
                     const int wd = u < nunits ? skey[u] : 0;
                     const int beg = wd & 1023, len = u < nunits ? (wd >> 10) & 15 : 0;
                     const int key = (wd >> 14) & 255, pc = (wd >> 22) & 63;
-                    uint32_t off[kRunBatch];
                     float ra[kRunBatch], rh[kRunBatch], rw[kRunBatch];
-#pragma unroll
-                    for (int v = 0; v < kRunBatch; ++v) {
-                        const bool act = v < len;
-                        const int4 e = srec[act ? beg + v : 0];
-                        off[v] = act ? (uint32_t)(e.x + ch) : (uint32_t)kOOBElem;
-                        ra[v] = act ? __builtin_bit_cast(float, e.y) : 0.f;
-                        rh[v] = act ? __builtin_bit_cast(float, e.z) : 0.f;
-                        rw[v] = act ? __builtin_bit_cast(float, e.w) : 0.f;
-                    }
                     float4 g[kRunBatch][kQPL];
 #pragma unroll
-                    for (int v = 0; v < kRunBatch; ++v)
-#pragma unroll
-                        for (int j = 0; j < kQPL; ++j)  // channels past D read zeros (out-of-range offset)
-                            g[v][j] = QuadBuf<T, 4>::load(gr, ch + 4 * j < D ? off[v] + 4 * j : (uint32_t)kOOBElem);
+                    for (int v = 0; v < kRunBatch; ++v) {
+                        const int4 e = srec[v < len ? beg + v : kChunkRecords];
+                        ra[v] = __builtin_bit_cast(float, e.y);
+                        rh[v] = __builtin_bit_cast(float, e.z);
+                        rw[v] = __builtin_bit_cast(float, e.w);
+                        load_row(g[v], e.x);
+                    }
                     Corners run = {};
 #pragma unroll
                     for (int v = 0; v < kRunBatch; ++v) {
@@ -1257,26 +1259,19 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
                 int cur = key_lo, pkey = -1;  // pkey: key of the finished run waiting in `pend`, or -1
                 Corners run = {}, pend = {};
                 for (int b = 0; b < span; b += kRunBatch) {
-                    uint32_t off[kRunBatch];
                     float ra[kRunBatch], rh[kRunBatch], rw[kRunBatch];
                     int rk[kRunBatch];
+                    float4 g[kRunBatch][kQPL];
 #pragma unroll
                     for (int u = 0; u < kRunBatch; ++u) {
                         const int pos = lo + b + u;
-                        const bool act = pos < hi;
-                        const int4 e = srec[act ? pos : 0];
-                        rk[u] = skey[act ? pos : 0];
-                        off[u] = act ? (uint32_t)(e.x + ch) : (uint32_t)kOOBElem;
-                        ra[u] = act ? __builtin_bit_cast(float, e.y) : 0.f;
-                        rh[u] = act ? __builtin_bit_cast(float, e.z) : 0.f;
-                        rw[u] = act ? __builtin_bit_cast(float, e.w) : 0.f;
+                        const int4 e = srec[pos < hi ? pos : kChunkRecords];
+                        rk[u] = skey[pos < hi ? pos : 0];
+                        ra[u] = __builtin_bit_cast(float, e.y);
+                        rh[u] = __builtin_bit_cast(float, e.z);
+                        rw[u] = __builtin_bit_cast(float, e.w);
+                        load_row(g[u], e.x);
                     }
-                    float4 g[kRunBatch][kQPL];
-#pragma unroll
-                    for (int u = 0; u < kRunBatch; ++u)
-#pragma unroll
-                        for (int j = 0; j < kQPL; ++j)  // channels past D read zeros (out-of-range offset)
-                            g[u][j] = QuadBuf<T, 4>::load(gr, ch + 4 * j < D ? off[u] + 4 * j : (uint32_t)kOOBElem);
 #pragma unroll
                     for (int u = 0; u < kRunBatch; ++u) {
                         const int pos = lo + b + u;
