@@ -111,9 +111,10 @@ msda_status_t msda_forward(const void* value, const int64_t* spatial_shapes,
  * anything else until the enqueued work completes. grad_value is then computed owner-by-owner:
  * samples are sorted by the pixel tile they touch and each grad_value row is written once by the
  * wave that owns its tile (rows of tiles seen by more than one chunk of 512 samples are added with
- * atomics). workspace may be NULL only where msda_backward_workspace_size(...,
- * MSDA_WORKSPACE_PREFERRED, ...) reports 0 bytes (small or sparse problems, and problems the
- * owner-computes path does not apply to): there grad_value is zeroed and accumulated with fp32
+ * atomics). Problems of few samples per level and slab are binned in one launch, in chunks down to
+ * 64 samples. workspace may be NULL only for small or
+ * sparse problems (fewer than one sample per two value rows, or at most 16384 samples) and those
+ * the owner-computes path does not apply to: there grad_value is zeroed and accumulated with fp32
  * atomics, as msda_backward_atomic does. Anywhere else a NULL workspace, or one smaller than
  * required, is MSDA_ERROR_INVALID_VALUE: the library never switches algorithms silently.
  *
@@ -148,7 +149,7 @@ msda_status_t msda_backward_atomic(const void* value, const int64_t* spatial_sha
  * loops, harnesses that forbid hipMalloc): msda_backward without a workspace argument and without
  * allocating anything. The owner-computes grad_value takes its scratch from a static device array
  * of MSDA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on until the process
- * ends; problems msda_backward would run without a workspace use fp32 atomics as it does. Results
+ * ends; problems msda_backward accepts without a workspace use fp32 atomics as it does then. Results
  * are those of msda_backward. All work runs on `stream` alone (no side stream). No hipMalloc,
  * hipFree or allocating runtime call is made; the first call on a device looks up the array's
  * address there.
@@ -156,8 +157,8 @@ msda_status_t msda_backward_atomic(const void* value, const int64_t* spatial_sha
  * Every call on one GPU shares that GPU's array: calls whose work overlaps on one GPU (on
  * different streams, or from different threads without ordering) race and give wrong grad_value.
  * The array keeps the last call's contents; everything that must start at zero is cleared by the
- * call itself. A problem whose workspace (msda_backward_workspace_size with
- * MSDA_WORKSPACE_PREFERRED) exceeds MSDA_NOALLOC_SCRATCH_BYTES is MSDA_ERROR_NOT_SUPPORTED
+ * call itself. A problem that needs a workspace (as msda_backward does) larger than
+ * MSDA_NOALLOC_SCRATCH_BYTES is MSDA_ERROR_NOT_SUPPORTED
  * (the DETR-encoder shape needs 82 MiB; the BEVFormer and Swin-feature shapes need more).
  * Pointer alignment and N*Lq == 0 as for msda_backward.
  */
@@ -194,8 +195,9 @@ msda_status_t msda_backward_deterministic(const void* value, const int64_t* spat
 
 /* Modes of msda_backward_workspace_size. */
 #define MSDA_WORKSPACE_PREFERRED 0 /* the workspace the library would use: 0 bytes where fp32 atomics
-                                      are expected to be faster (fewer than one sample per two value
-                                      rows, or at most 16384 samples)                               */
+                                      are expected to be faster: of the problems msda_backward accepts
+                                      without one, all but those of few samples per level and slab
+                                      whose atomics outlast binning and folding every value row   */
 #define MSDA_WORKSPACE_OWNER 1     /* the owner-computes workspace whenever that path applies      */
 #define MSDA_WORKSPACE_DETERMINISTIC 2 /* the workspace of msda_backward_deterministic                */
 

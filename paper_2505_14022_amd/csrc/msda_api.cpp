@@ -222,6 +222,15 @@ SideStream* side_stream(int dev) {
     return x.s ? &x : nullptr;
 }
 
+// Whether msda_backward runs without a workspace, on fp32 atomics.
+bool atomics_accepted(const int64_t* shapes, const int64_t* starts, int64_t N, int64_t S, int64_t M, int64_t D,
+                      int64_t Lq, int64_t L, int64_t P) {
+    const int64_t nb = batch_per_launch(S, M, D, Lq, L, P);
+    msda::Params p = base_params(shapes, starts, S, M, D, Lq, L, P);
+    p.n_batch = (int)(N < nb ? N : nb);
+    return msda::atomics_suffice(p);
+}
+
 // Shared body of both backward entry points (arguments already checked, except value / grad_out /
 // grad_value). `pro` is null for the plain entry point; with it, each batch chunk first computes
 // its locations and weights into the staging buffers of `smp` and ends with the prologue's gradient.
@@ -250,7 +259,8 @@ msda_status_t backward_body(const void* value, const int64_t* shapes, const int6
 #ifdef MSDA_ABLATE_ONE_STREAM
     one_stream = true;
 #endif
-    // a problem binned slab by slab is over before a second stream would pay for its two events
+    // a problem binned slab by slab is over before a second stream would pay for its two events: with one,
+    // 21 thousand to 1.8 M samples took up to 37 us longer, none less
     bool small = false;
     if (binned) {
         msda::Params p = base_params(shapes, starts, S, M, D, Lq, L, P);
@@ -442,16 +452,12 @@ msda_status_t msda_backward(const void* value, const int64_t* spatial_shapes, co
                             workspace_bytes, need);
             if (!aligned(workspace, 256)) return fail(MSDA_ERROR_INVALID_VALUE, "workspace must be 256-byte aligned");
             binned = true;
-        } else if (need > 0) {
-            // no workspace: only where the library itself prefers fp32 atomics (small or sparse
-            // problems); elsewhere the caller chooses msda_backward_atomic explicitly
-            size_t preferred = 0;
-            msda_backward_workspace_size(spatial_shapes, level_start_index, N, S, M, D, Lq, L, P, dtype,
-                                         MSDA_WORKSPACE_PREFERRED, &preferred);
-            if (preferred > 0)
-                return fail(MSDA_ERROR_INVALID_VALUE,
-                            "msda_backward needs a workspace of %zu bytes for this problem (or call "
-                            "msda_backward_atomic)", preferred);
+        } else if (need > 0 && !atomics_accepted(spatial_shapes, level_start_index, N, S, M, D, Lq, L, P)) {
+            // no workspace: only where fp32 atomics are accepted (small or sparse problems);
+            // elsewhere the caller chooses msda_backward_atomic explicitly
+            return fail(MSDA_ERROR_INVALID_VALUE,
+                        "msda_backward needs a workspace of %zu bytes for this problem (or call "
+                        "msda_backward_atomic)", need);
         }
     }
     Sampling smp = {sampling_loc, attn_weight, grad_loc, grad_attn};
@@ -498,11 +504,12 @@ msda_status_t msda_backward_noalloc(const void* value, const int64_t* spatial_sh
                         "misaligned pointer: value and grad_out need 16 bytes, sampling_loc and grad_loc 8, "
                         "attn_weight and grad_attn 4");
     }
-    // the workspace msda_backward would prefer: none (fp32 atomics) for small or sparse problems
+    // small or sparse problems that msda_backward accepts without a workspace run on fp32 atomics, and so use
+    // nothing that calls on other streams share
     size_t need = 0;
-    if (Lq > 0) {
+    if (Lq > 0 && !atomics_accepted(spatial_shapes, level_start_index, N, S, M, D, Lq, L, P)) {
         st = msda_backward_workspace_size(spatial_shapes, level_start_index, N, S, M, D, Lq, L, P, dtype,
-                                          MSDA_WORKSPACE_PREFERRED, &need);
+                                          MSDA_WORKSPACE_OWNER, &need);
         if (st != MSDA_SUCCESS) return st;
     }
     if (need > msda::kStaticScratchBytes)

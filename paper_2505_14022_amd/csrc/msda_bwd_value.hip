@@ -526,6 +526,10 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(Params p) {
 // memory, no scans over workgroups and no atomics but one per workgroup for its work items. It
 // takes 20-30 us, of which the chain of its phases on one CU is most (5376 to 9000 samples per
 // level: 20 and 31 us, against 45-55 us of kernels and five launches for the passes above).
+// A work item is a word, its tile and the chunk of the tile's records, beside one descriptor per tile: a descriptor
+// per item of 64 records would need up to a quarter more workspace than the passes above.
+constexpr int kItemChunkBits = 11;           // a tile's chunks: at most 16384 records by 64
+constexpr int kSlabMaxTiles = 1 << 20;       // the tiles that the rest of a (non-negative) word numbers
 constexpr int kSlabThreads = 1024;
 constexpr int kSlabSamples = 16 * kSlabThreads;  // samples of a (slab, level) that one workgroup bins
 template <int HELD>  // samples of a thread, held in registers
@@ -651,15 +655,13 @@ __global__ __launch_bounds__(kSlabThreads) void bin_slab_kernel(Params p) {
         const Visible v = visible(t);
         const int nvis = v.na + v.nb + v.nc + v.nd;
         const int nit = nvis > 0 ? (nvis + p.item_records - 1) / p.item_records : 1;
-        for (int c = 0; c < nit; ++c, ++item) {
-            if (item >= p.max_items) break;
-            int4* d = reinterpret_cast<int4*>(p.item_desc) + (size_t)item * 4;
-            const int beg = c * p.item_records;
-            d[0] = make_int4(beg, min(beg + p.item_records, nvis), nit > 1, l);
-            d[1] = make_int4(n, m, ty * kTileEdge, tx * kTileEdge);
-            d[2] = make_int4(rec0 + v.a0, v.na, rec0 + v.b0, v.nb);
-            d[3] = make_int4(rec0 + v.c0, v.nc, rec0 + v.d0, 0);
-        }
+        const int tile = slab * p.tiles_per_slab + s_geo[5 * kMaxLevels + l] + t;
+        int4* d = reinterpret_cast<int4*>(p.item_desc) + (size_t)tile * 4;
+        d[0] = make_int4(0, nvis, nit > 1, l);
+        d[1] = make_int4(n, m, ty * kTileEdge, tx * kTileEdge);
+        d[2] = make_int4(rec0 + v.a0, v.na, rec0 + v.b0, v.nb);
+        d[3] = make_int4(rec0 + v.c0, v.nc, rec0 + v.d0, 0);
+        for (int c = 0; c < nit && item < p.max_items; ++c, ++item) p.items[item] = tile << kItemChunkBits | c;
     }
     // rows of tiles that several work items add into start at zero: a pixel per lane
     for (int t = wave; t < tiles; t += kSlabThreads / 64) {
@@ -1009,7 +1011,23 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     auto item_at = [&](int q, int s) { return qbase(q) + s; };
     auto counter = [&](int q) { return p.queue + q * kQueueStride; };
     // descriptor of work item `it` (its block of channels is it % p.ch_blocks): lanes 0..15 hold its 16 words
-    auto load_desc = [&](int it) { return lane < 16 ? p.item_desc[(size_t)(it / p.ch_blocks) * 16 + lane] : 0; };
+    // words of this wave's first 64 items, one per lane
+    const int first = blockIdx.x * kAccWaves + wave;
+    const int ahead = first + lane * nwaves;
+    const int words = fixed && ahead < total ? p.items[ahead / p.ch_blocks] : 0;
+    auto load_desc = [&](int it) {
+        int row = it / p.ch_blocks, chunk = 0;
+        if (fixed) {
+            const int k = (it - first) / nwaves;
+            const int word = k < 64 ? __builtin_amdgcn_readlane(words, k) : __builtin_amdgcn_readfirstlane(p.items[row]);
+            row = word >> kItemChunkBits;
+            chunk = word & ((1 << kItemChunkBits) - 1);
+        }
+        int v = lane < 16 ? p.item_desc[(size_t)row * 16 + lane] : 0;
+        if (fixed && lane == 0) v = chunk * p.item_records;
+        if (fixed && lane == 1) v = min((chunk + 1) * p.item_records, v);
+        return v;
+    };
     // the item's visible records, kRecPerLane per lane (all loads in flight together); rows past
     // the item's end are marked with x = -1
     auto load_records = [&](int dv, int4 (&rc)[kRecPerLane]) {
@@ -1031,7 +1049,7 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
             rc[i] = idx >= 0 && idx < p.n_samples ? records[idx] : make_int4(-1, 0, 0, 0);
         }
     };
-    int taken = blockIdx.x * kAccWaves + wave;
+    int taken = first;
     if (!fixed && lane == 0) taken = atomicAdd(counter(owner), 1);
     int pf_item = -1, pf_dv = 0;  // the next item of this queue and its prefetched descriptor
     for (;;) {
@@ -1407,17 +1425,6 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(Params p) {
 
 // ---------------------------------------------------------------- host side
 
-bool prefer_atomic(const Params& p) {
-    const int64_t samples = (int64_t)p.n_batch * p.Lq * p.M * p.K;
-    // Below one sample per two value rows the binned path's fixed cost (every tile of every slab is
-    // folded and stored) outweighs the atomics it saves: at the DETR-decoder shape the two paths
-    // break even near 0.8 samples per row, and atomics take 40 % of the binned time at 0.24.
-    if (2 * samples < (int64_t)p.n_batch * p.S * p.M) return true;
-    // Small problems likewise: the binned path's nine launches cost about 80 us at 128 samples, while
-    // atomics from at most 16384 samples take a few microseconds even when they all hit one row.
-    return samples <= kAtomicMaxSamples;
-}
-
 namespace {
 // Whether one workgroup per (slab, level) bins the problem (bin_slab_kernel): where the samples of a
 // level fit its registers, and up to 2 M samples, beyond which the many-workgroup passes, beside
@@ -1430,6 +1437,34 @@ bool slab_bins_apply(const Params& p) {
            (int64_t)p.n_batch * p.Lq * p.M * p.K <= kSlabMaxSamples;
 }
 
+}  // namespace
+
+bool atomics_suffice(const Params& p) {
+    const int64_t samples = (int64_t)p.n_batch * p.Lq * p.M * p.K;
+    // Below one sample per two value rows the many-workgroup binned path's fixed cost (every tile of
+    // every slab is folded and stored) outweighs the atomics it saves: at the DETR-decoder shape the two
+    // paths break even near 0.8 samples per row, and atomics take 40 % of the binned time at 0.24.
+    if (2 * samples < (int64_t)p.n_batch * p.S * p.M) return true;
+    // Small problems likewise: atomics from at most 16384 samples take a few microseconds even when
+    // they all hit one row (128 samples: 10 us, against 35 us of three launches binned slab by slab).
+    return samples <= kAtomicMaxSamples;
+}
+
+bool prefer_atomic(const Params& p) {
+    if (!atomics_suffice(p)) return false;
+    const int64_t samples = (int64_t)p.n_batch * p.Lq * p.M * p.K;
+    if (samples <= kAtomicMaxSamples || !slab_bins_apply(p) || p.D % 4 != 0) return true;
+    // Binned slab by slab, a sparse problem pays some 20 us more of launches and latency and 0.06 ns more per
+    // value row and block of 32 channels (its tiles are folded, not only cleared), and saves its atomics, which
+    // run at 20.5 G pieces of 64 bytes a second. Backward us on atomics against binned, 8 heads of 32 channels, 300
+    // queries of 16 samples over 17 821 pixels: batch 2 48 / 57, 3 65 / 67, 4 81 / 79, 8 147 / 125; 100
+    // queries at batch 8 77 / 97; 16 channels at batch 8 86 / 117.
+    const double atomic_ns = 4.0 * samples * ((p.D + 15) / 16) / 20.5;
+    const double rows = (double)p.n_batch * p.S * p.M * ((p.D + 31) / 32);
+    return atomic_ns < 20000.0 + 0.06 * rows;
+}
+
+namespace {
 // Work items of a problem binned by bin_slab_kernel: the blocks of 32 channels are items of their own,
 // and a tile is cut into as few records per item (at least 64) as leaves every item a wave of the
 // fold's resident grid: an item's latency, not the sums, is what such a fold takes (64 thousand
@@ -1549,6 +1584,7 @@ bool plan_binned(Params& p) {
     p.item_records = kChunkRecords;
     p.ch_blocks = 1;
     p.slab_bins = runs && slab_bins_apply(p);
+    if (n_tiles > kSlabMaxTiles) p.slab_bins = 0;
     if (p.slab_bins) pick_small_items(p);
     const int64_t max_items = 2 * n_tiles + 4 * n_samples / p.item_records + 1;
     if (n_bins + 1 > kMaxIndex || max_items > kMaxIndex || n_samples > kMaxIndex) return false;
@@ -1611,11 +1647,16 @@ size_t deterministic_extra_bytes(const Params& p) {
            align256((size_t)p.max_items * kRunPix * p.D * 4);
 }
 
+// Descriptors that the workspace holds, in work items of kChunkRecords records. Binned slab by slab, these are the
+// tiles' descriptors and the items' words: 64 bytes a tile, and 4 an item, of which there are at most one
+// per tile and one per 16 samples (each in up to four tiles, 64 records an item).
+size_t desc_rows(const Params& p) { return 2 * (size_t)p.n_tiles + 4 * (size_t)p.n_samples / kChunkRecords + 1; }
+
 size_t binned_workspace_bytes(const Params& p) {
     const size_t nb = (size_t)p.n_bins;
-    return align256(zeroed_ints(p) * 4) + align256((size_t)p.max_items * 64) + align256((nb + 1) * 4) + align256(nb * 4) +
+    return align256(zeroed_ints(p) * 4) + align256(desc_rows(p) * 64) + align256((nb + 1) * 4) + align256(nb * 4) +
            align256(((size_t)p.n_tiles + 1) * 4) +
-           align256((size_t)p.max_items * 4) + align256((size_t)p.scan_blocks * 2 * 4) +
+           align256(desc_rows(p) * 4) + align256((size_t)p.scan_blocks * 2 * 4) +
            align256((size_t)p.n_samples * 16) + deterministic_extra_bytes(p);
 }
 
@@ -1627,15 +1668,15 @@ void bind_workspace(Params& p, void* ws) {
     p.scan_done = p.queue + kQueues * kQueueStride;
     c += align256(zeroed_ints(p) * 4);
     p.item_desc = reinterpret_cast<int*>(c);
-    c += align256((size_t)p.max_items * 64);
+    c += align256(desc_rows(p) * 64);
     p.offsets = reinterpret_cast<int*>(c);
     c += align256((nb + 1) * 4);
     p.cursor = reinterpret_cast<int*>(c);
     c += align256(nb * 4);
     p.tile_chunks = reinterpret_cast<int*>(c);
     c += align256(((size_t)p.n_tiles + 1) * 4);
-    p.items = reinterpret_cast<int*>(c);
-    c += align256((size_t)p.max_items * 4);
+    p.items = p.slab_bins ? p.item_desc + (size_t)p.n_tiles * 16 : reinterpret_cast<int*>(c);
+    c += align256(desc_rows(p) * 4);
     p.block_sums = reinterpret_cast<int*>(c);
     c += align256((size_t)p.scan_blocks * 2 * 4);
     p.records = reinterpret_cast<int*>(c);

@@ -136,11 +136,11 @@ struct Params {
     int* queue;                 // [8 * 64]            fold work queue counters, 256 B apart (zeroed with counts)
     int* scan_done;             // [1]                 workgroups of the scan's first pass done, or with slab_bins
                                 //                     the number of work items (zeroed with counts)
-    int* item_desc;             // [max_items * 16]    fold work item descriptors
+    int* item_desc;             // [max_items * 16]    fold work item descriptors (slab_bins: [n_tiles * 16], of tiles)
     int* offsets;               // [n_bins + 1]        exclusive prefix of counts
     int* cursor;                // [n_bins]            fill position per bin
     int* tile_chunks;           // [n_tiles + 1]       exclusive prefix of work items per tile
-    int* items;                 // [max_items]         work item -> tile
+    int* items;                 // [max_items]         work item -> tile (slab_bins: tile and chunk of its records)
     int* block_sums;            // [2 * scan_blocks]
     int* records;               // [n_samples][4]      {grad_out row, a, h_im, w_im} per sample, sorted by bin
     int* chunk_hist;            // [n_slabs * chunks][bins_per_slab] (deterministic) records per counting
@@ -187,7 +187,9 @@ int device_cu_count(hipStream_t stream);
 // first call for that device; no allocation.
 hipError_t static_scratch(int device, void** ptr);
 
-// True when fp32 atomics are expected to beat the binned grad_value path (sparse or small problems).
+// True for the sparse or small problems that msda_backward runs on fp32 atomics when it has no workspace.
+bool atomics_suffice(const Params& p);
+// True when fp32 atomics are expected to beat the binned grad_value path: not beyond atomics_suffice.
 bool prefer_atomic(const Params& p);
 // Chooses tile sizes for the binned grad_value path and fills the geometry fields of `p`.
 // Returns false if the path does not apply (then grad_value uses atomics).

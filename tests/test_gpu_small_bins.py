@@ -5,8 +5,8 @@ all off the map. Tolerances are those of the parity tests."""
 import numpy as np
 import pytest
 
-from paper_2505_14022_amd import workloads
-from gpu_util import check_parity, require_gpu
+from paper_2505_14022_amd import msda, workloads
+from gpu_util import TOL_GRAD_ATTN, TOL_GRAD_LOC, TOL_GRAD_VALUE, check_parity, require_gpu
 
 CASES = [
     # N, M, D, levels, P, Lq, dtype
@@ -40,3 +40,56 @@ def test_small_bins_degenerate(where):
     else:
         inp.loc[...] = np.float32(-0.5)
     check_parity(inp, workspace="owner")
+
+
+# Sparse problems where "auto" bins slab by slab (their atomics would outlast it), beside the same calls on atomics
+# (no workspace).
+ROUTES = [
+    # N, M, D, levels, P, Lq, dtype, "auto" has a workspace
+    (8, 8, 32, ((100, 134), (50, 67), (25, 34), (13, 17)), 4, 300, "f32", True),
+    (3, 16, 48, ((61, 83), (31, 41)), 4, 350, "f16", True),
+    (8, 8, 32, ((100, 134), (50, 67), (25, 34), (13, 17)), 4, 60, "f16", False),
+    (2, 3, 36, ((17, 23), (9, 11)), 4, 1500, "f32", True),
+]
+
+
+def host_sizes(case):
+    import torch
+
+    N, M, D, levels, P, Lq, _, _ = case
+    shapes = torch.tensor(levels)
+    area = shapes.prod(1)
+    starts = torch.cumsum(area, 0) - area
+    return [msda.workspace_size(shapes, starts, N, int(area.sum()), M, D, Lq, len(levels), P, 0, mode)
+            for mode in (msda.MSDA_WORKSPACE_PREFERRED, msda.MSDA_WORKSPACE_OWNER)]
+
+
+@pytest.mark.parametrize("case", ROUTES, ids=lambda c: f"N{c[0]}_M{c[1]}_Lq{c[5]}")
+def test_preferred_route(case):
+    preferred, owner = host_sizes(case)
+    assert owner > 0 and preferred == (owner if case[7] else 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", ROUTES, ids=lambda c: f"N{c[0]}_M{c[1]}_Lq{c[5]}")
+def test_routes_agree(case):
+    """Each route against the others: sums of the same fp32 terms in different orders, so within
+    the parity bounds."""
+    import torch
+
+    require_gpu()
+    N, M, D, levels, P, Lq, dtype, _ = case
+    inp = workloads.random_case(N, M, D, levels, P, Lq, dtype=dtype, seed=D + Lq)
+    t = {k: torch.from_numpy(np.ascontiguousarray(getattr(inp, k))).cuda()
+         for k in ("value", "loc", "attn", "grad_out")}
+    shapes = torch.tensor(levels)
+    area = shapes.prod(1)
+    starts = torch.cumsum(area, 0) - area
+
+    def run(workspace):
+        return msda.backward(t["value"], shapes, starts, t["loc"], t["attn"], t["grad_out"], workspace=workspace)
+
+    want = run(None)
+    for got in (run("auto"), run("owner")):
+        for g, w, tol in zip(got, want, (TOL_GRAD_VALUE, TOL_GRAD_LOC, TOL_GRAD_ATTN)):
+            assert float((g - w).abs().max()) <= tol * float(w.abs().max())
