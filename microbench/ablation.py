@@ -62,8 +62,8 @@ VARIANTS = {
 }
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Xclang", "-target-feature",
          "-Xclang", "-packed-fp32-ops", "-munsafe-fp-atomics"]
-SOURCES = ["msda_api.cpp", "msda_fwd.hip", "msda_bwd.hip", "msda_bwd_value.hip", "msda_prologue.hip",
-           "msda_noalloc.hip"]
+SOURCES = ["msda_api.cpp", "msda_arrange.cpp", "msda_fwd.hip", "msda_bwd.hip", "msda_bwd_value.hip",
+           "msda_prologue.hip", "msda_noalloc.hip"]
 PASSES = {
     "sq": ["SQ_WAVES", "SQ_WAVE_CYCLES", "SQ_BUSY_CYCLES", "SQ_INSTS_VALU", "SQ_INSTS_LDS", "SQ_LDS_BANK_CONFLICT",
            "SQ_WAIT_INST_ANY", "SQ_ACTIVE_INST_VALU", "GRBM_GUI_ACTIVE"],

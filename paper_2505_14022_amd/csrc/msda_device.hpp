@@ -10,8 +10,7 @@
 namespace msda {
 namespace {
 
-constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / 64;
+constexpr int kBlock = 64 * kWaves;
 constexpr int kMaxItems = 128;  // (query, sample) items parked in LDS per wave per phase
 constexpr uint32_t kOOBElem = uint32_t(kMaxLaunchElems);
 constexpr int kBufFlags = 0x00020000;  // buffer resource word 3 for gfx9: 32-bit data format
@@ -252,81 +251,11 @@ __device__ __forceinline__ float2 group_softmax_stats(float z, int G) {
 
 // ---------------------------------------------------------------- work decomposition
 
-struct Tile {
-    int n, m, q0;  // slab (n, m) and the first query (place in the query order, see query_at) of this wave
-    int part;      // which of the p.k_split parts of the queries' samples this workgroup takes
-};
-
-// Workgroup -> (slab, query chunk). Workgroup b runs on XCD b % 8 (the dispatcher deals workgroups
-// to the eight XCDs in turn); with i = b / 8, XCD x takes its work in one of two arrangements:
-//  * query eighths (p.xcd_split): the x-th eighth of every slab's query chunks, slab after slab. The
-//    grid is 8 * slabs * ceil(chunks / 8); a workgroup past the end of its eighth exits. With
-//    p.xcd_bands the eighths are bands of rows instead: XCD x takes the chunks whose first query lies
-//    in the x-th eighth of the rows of its level (at most p.band_cap per slab; the grid is
-//    8 * slabs * band_cap and a workgroup past the end of its band exits).
-//  * slab ranges: the contiguous range [x*G/8, (x+1)*G/8) of the work items in slab-major order, so
-//    that each slab's rows are read through one XCD's L2. The grid is a multiple of 8.
+// The work of this wave (false: none).
 __device__ __forceinline__ bool tile_of(const Params& p, int PPW, Tile& t) {
-    const uint32_t G = gridDim.x;
-    const uint32_t b = blockIdx.x;
     int slab, chunk;
-    if (p.xcd_bands) {
-        // XCD x takes, slab after slab, the query chunks whose first query lies in the x-th eighth of
-        // the rows of its level
-        const int x = (int)(b & 7u), i = (int)(b >> 3);
-        slab = i / p.band_cap;
-        int k = i - slab * p.band_cap;
-        if (slab >= p.n_batch * p.M / p.head_group || k >= p.band_count[x]) return false;
-        chunk = -1;
-        for (int l = 0; l < p.L; ++l) {
-            const int c0 = p.band_c[l][x], n = p.band_c[l][x + 1] - c0;
-            if (k < n) {
-                chunk = c0 + k;
-                break;
-            }
-            k -= n;
-        }
-        if (chunk < 0) return false;
-    } else if (p.xcd_split) {
-        const int x = (int)(b & 7u), i = (int)(b >> 3);
-        const int per = (p.chunks + 7) >> 3;
-        slab = i / per;
-        chunk = (int)(((int64_t)x * p.chunks) >> 3) + (i - slab * per);
-        if (slab >= p.n_batch * p.M / p.head_group || chunk >= (int)(((int64_t)(x + 1) * p.chunks) >> 3)) return false;
-    } else {
-#ifndef MSDA_ABLATE_NO_XCD_REMAP
-        const uint32_t w = (b & 7u) * (G >> 3) + (b >> 3);
-#else
-        const uint32_t w = b;
-        (void)G;
-#endif
-        if (w >= (uint32_t)p.num_blocks) return false;
-#ifndef MSDA_ABLATE_HEAD_FASTEST
-        slab = (int)(w / (uint32_t)p.chunks);
-        chunk = (int)(w - (uint32_t)slab * (uint32_t)p.chunks);
-#else
-        // work items ordered (batch, query chunk, head): the heads of one chunk are consecutive
-        const int nc = (int)(w / (uint32_t)p.M);
-        const int m = (int)(w - (uint32_t)nc * (uint32_t)p.M);
-        const int n = nc / p.chunks;
-        chunk = nc - n * p.chunks;
-        slab = n * p.M + m;
-#endif
-    }
-    // slabs are taken p.head_group at a time: the heads of one group share cache lines, so the waves of
-    // a workgroup take the same queries of all of them
-    const int groups = p.M / p.head_group;
-    const int waves = p.q_per_block / PPW;  // waves per head
-    const int wave = (int)(threadIdx.x >> 6), hg = wave / waves;
-    t.n = slab / groups;
-    t.m = (slab - t.n * groups) * p.head_group + hg;
-    t.part = 0;
-    if (p.k_split > 1) {
-        // the parts of one query chunk are consecutive work items
-        t.part = chunk % p.k_split;
-        chunk /= p.k_split;
-    }
-    t.q0 = chunk * p.q_per_block + (wave - hg * waves) * PPW;
+    if (!block_work(p, blockIdx.x, gridDim.x, slab, chunk)) return false;
+    t = wave_work(p, PPW, slab, chunk, (int)(threadIdx.x >> 6));
     return true;
 }
 
@@ -342,40 +271,6 @@ __device__ __forceinline__ int query_at(const Params& p, const int* s_lvl, int i
         if (i >= p.start[j]) l = j;
     const int st = s_lvl[2 * kMaxLevels + l];
     return st + strip_pixel(i - st, s_lvl[l], s_lvl[kMaxLevels + l], p.strip_rows);
-}
-
-// The arrangement of tile_of. Query eighths when there are at least half as many queries as value
-// pixels (self-attention over the maps: a query's reference point follows the query order, so an
-// eighth of the queries reads a band of every level, and an XCD's L2 holds the bands of several
-// slabs at once). Slab ranges otherwise (cross-attention: a query samples anywhere in its slab, so
-// the working set is the slab, and fewer slabs per L2 is better). Measured with both arrangements:
-// the forward 6 % faster at the DETR-encoder shape, 5-16 % at the Swin shape and 10-22 % at the
-// BEV-temporal shape with eighths; 4 % (BEV-spatial) and 40 % (DETR-decoder) slower with them.
-inline bool xcd_split(const Params& p) {
-#if defined(MSDA_ABLATE_SLAB_RANGES) || defined(MSDA_ABLATE_NO_XCD_REMAP) || defined(MSDA_ABLATE_HEAD_FASTEST)
-    (void)p;
-    return false;
-#elif defined(MSDA_ABLATE_QUERY_EIGHTHS)
-    (void)p;
-    return true;
-#else
-    return 2 * (int64_t)p.Lq >= p.S;
-#endif
-}
-
-// Whether the query eighths follow the rows of the maps instead of the query index: for
-// self-attention over the maps (as many queries as value pixels, query q at pixel q in level-major
-// order). With eighths of the query index, the XCDs that hold the coarse levels' queries read every
-// level over the whole map; with bands of rows every XCD reads one band of each level. Same-box A/B:
-// Swin-feature shape forward 256 -> 238 us, backward 841 -> 820 us; DETR-encoder and one-level
-// BEV shapes within 1 %. If the queries are in another order only the speed changes.
-inline bool xcd_bands(const Params& p) {
-#ifdef MSDA_ABLATE_INDEX_EIGHTHS
-    (void)p;
-    return false;
-#else
-    return p.Lq == p.S;
-#endif
 }
 
 // The level of sample k of a query.
@@ -480,57 +375,13 @@ inline int pick_lpp(int D, int vec) {
     return lpp;
 }
 
-// Launches KernelT<T, VEC, lpp>::fn() over (slab, query chunk) workgroups of kBlock lanes, or of
-// one wave each when that many workgroups would leave CUs idle: a wave's work does not depend on
-// the other waves of its workgroup, and at the DETR-decoder shape (160 four-wave workgroups)
-// one-wave workgroups spread the grad_value atomics over all CUs.
-constexpr int kSmallGrid = 1024;
-#ifndef MSDA_KSPLIT_WAVES
-#define MSDA_KSPLIT_WAVES 4096
-#endif
-constexpr int64_t kSplitWaves = MSDA_KSPLIT_WAVES;  // waves a sample split may grow the grid to
-#ifndef MSDA_KSPLIT_MIN
-#define MSDA_KSPLIT_MIN 4
-#endif
-constexpr int kSplitMinSamples = MSDA_KSPLIT_MIN;
+// Launches KernelT<T, VEC, lpp>::fn() over the work that plan_gather lays out.
 template <template <typename, int, int> class KernelT, typename T, int VEC>
 hipError_t launch_lpp(Params p, int lpp, hipStream_t stream) {
     auto go = [&](auto kernel, int ppw) -> hipError_t {
-        const int64_t chunks4 = (p.Lq + kWaves * ppw - 1) / (kWaves * ppw);
-        const int waves = (int64_t)p.n_batch * p.M * chunks4 < kSmallGrid ? 1 : kWaves;
-        // Strips of rows where the queries are the pixels (as many queries as pixels; if they are in
-        // another order only the speed changes), and two heads per workgroup where two heads' rows of
-        // one pixel are one 128-byte cache line. Forward / backward us before and after, same box:
-        // Swin-feature shape fp16 188 / 853 -> 151 / 811, BEV-temporal fp16 207 / 792 -> 186 / 751,
-        // DETR-encoder fp32 91 / 300 -> 89 / 293 (its 128-byte rows hit the cache more often, and its
-        // loads run at 0.7 of the cache's rate). Strips of 16 rows were 2-5 % slower, of 4 rows 1-15 %
-        // in the backward; workgroups of 8 or 16 waves were slower.
-        p.strip_rows = waves > 1 && xcd_split(p) && xcd_bands(p) && p.S < kStripMaxPixels ? kStripRows : 0;
-        p.head_group = waves > 1 && p.M % 2 == 0 && p.D * (int)sizeof(T) == 64 ? 2 : 1;
-        p.q_per_block = waves * ppw / p.head_group;
-        const int qchunks = (p.Lq + p.q_per_block - 1) / p.q_per_block;
-        // a grid too small to fill the chip splits each query's samples over up to k_split_max
-        // work items, as long as a part keeps kSplitMinSamples samples
-        int ks = 1;
-        while (2 * ks <= p.k_split_max && 2 * ks * kSplitMinSamples <= p.K &&
-               (int64_t)p.n_batch * p.M * qchunks * (p.q_per_block / ppw) * 2 * ks <= kSplitWaves)
-            ks *= 2;
-        p.k_split = ks;
-        p.chunks = qchunks * ks;
-        const int n_groups = p.n_batch * p.M / p.head_group;
-        p.num_blocks = n_groups * p.chunks;
-        if (p.num_blocks == 0) return hipSuccess;
-        const int64_t split_grid = 8 * (int64_t)n_groups * ((p.chunks + 7) / 8);
-        p.xcd_split = xcd_split(p) && split_grid <= INT32_MAX;
-        p.xcd_bands = 0;
-        int64_t band_grid = 0;
-        if (p.xcd_split && ks == 1 && xcd_bands(p)) {
-            set_bands(p);
-            band_grid = 8 * (int64_t)n_groups * p.band_cap;
-            p.xcd_bands = band_grid <= INT32_MAX;
-        }
-        const int grid = p.xcd_bands ? (int)band_grid : p.xcd_split ? (int)split_grid : (p.num_blocks + 7) / 8 * 8;
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), 0, stream, p);
+        const GatherLaunch g = plan_gather(p, ppw, (int)sizeof(T));
+        if (g.grid == 0) return hipSuccess;
+        hipLaunchKernelGGL(kernel, dim3(g.grid), dim3(64 * g.waves), 0, stream, p);
         return hipGetLastError();
     };
     switch (lpp) {

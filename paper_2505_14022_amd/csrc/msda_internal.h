@@ -35,6 +35,20 @@ constexpr int kMaxLevels = MSDA_MAX_LEVELS;
 constexpr int64_t kMaxLaunchElems = int64_t(1) << 29;
 constexpr int64_t kMaxIndex = (int64_t(1) << 31) - 1;
 
+// Waves of a workgroup of the gather kernels, or one where that many workgroups would leave CUs idle: a
+// wave's work does not depend on the other waves of its workgroup, and at the DETR-decoder shape
+// (160 four-wave workgroups) one-wave workgroups spread the grad_value atomics over all CUs.
+constexpr int kWaves = 4;
+constexpr int kSmallGrid = 1024;
+#ifndef MSDA_KSPLIT_WAVES
+#define MSDA_KSPLIT_WAVES 4096
+#endif
+constexpr int64_t kSplitWaves = MSDA_KSPLIT_WAVES;  // waves a sample split may grow the grid to
+#ifndef MSDA_KSPLIT_MIN
+#define MSDA_KSPLIT_MIN 4
+#endif
+constexpr int kSplitMinSamples = MSDA_KSPLIT_MIN;
+
 // Owner-computes grad_value: limits of the binned path.
 constexpr int kHistMax = 15872;      // bins of one (n, m) slab counted in LDS (62 KB)
 constexpr int kTileFloats = 3200;    // LDS floats of one tile accumulator with its margin (12.5 KB per wave)
@@ -147,6 +161,93 @@ struct Params {
                                 //                     workgroup and bin, then their prefix over workgroups
     float* partials;            // [max_items][64][D]  (deterministic) sums of the work items of split tiles
 };
+
+// Workgroup -> (slab group, query chunk); false: no work. A slab group is p.head_group heads of a batch item, in
+// (batch, head) order. Workgroup b of G runs on XCD b % 8 (the dispatcher deals workgroups
+// to the eight XCDs in turn); with i = b / 8, XCD x takes its work in one of two arrangements:
+//  * query eighths (p.xcd_split): the x-th eighth of every slab group's query chunks, group after group. The
+//    grid is 8 * groups * ceil(chunks / 8); a workgroup past the end of its eighth exits. With
+//    p.xcd_bands the eighths are bands of rows instead: XCD x takes the chunks whose first query lies
+//    in the x-th eighth of the rows of its level (at most p.band_cap per group; the grid is
+//    8 * groups * band_cap and a workgroup past the end of its band exits).
+//  * slab ranges: the contiguous range [x*G/8, (x+1)*G/8) of the work items in slab-major order, so
+//    that each slab's rows are read through one XCD's L2. The grid is a multiple of 8.
+__host__ __device__ inline bool block_work(const Params& p, uint32_t b, uint32_t G, int& slab, int& chunk) {
+    if (p.xcd_bands) {
+        const int x = (int)(b & 7u), i = (int)(b >> 3);
+        slab = i / p.band_cap;
+        int k = i - slab * p.band_cap;
+        if (slab >= p.n_batch * p.M / p.head_group || k >= p.band_count[x]) return false;
+        chunk = -1;
+        for (int l = 0; l < p.L; ++l) {
+            const int c0 = p.band_c[l][x], n = p.band_c[l][x + 1] - c0;
+            if (k < n) {
+                chunk = c0 + k;
+                break;
+            }
+            k -= n;
+        }
+        return chunk >= 0;
+    }
+    if (p.xcd_split) {
+        const int x = (int)(b & 7u), i = (int)(b >> 3);
+        const int per = (p.chunks + 7) >> 3;
+        slab = i / per;
+        chunk = (int)(((int64_t)x * p.chunks) >> 3) + (i - slab * per);
+        return slab < p.n_batch * p.M / p.head_group && chunk < (int)(((int64_t)(x + 1) * p.chunks) >> 3);
+    }
+#ifndef MSDA_ABLATE_NO_XCD_REMAP
+    const uint32_t w = (b & 7u) * (G >> 3) + (b >> 3);
+#else
+    const uint32_t w = b;
+    (void)G;
+#endif
+    if (w >= (uint32_t)p.num_blocks) return false;
+#ifndef MSDA_ABLATE_HEAD_FASTEST
+    slab = (int)(w / (uint32_t)p.chunks);
+    chunk = (int)(w - (uint32_t)slab * (uint32_t)p.chunks);
+#else
+    // work items ordered (batch, query chunk, head group): the heads of one chunk are consecutive
+    const int groups = p.M / p.head_group;
+    const int nc = (int)(w / (uint32_t)groups);
+    const int n = nc / p.chunks;
+    chunk = nc - n * p.chunks;
+    slab = n * groups + (int)(w - (uint32_t)nc * (uint32_t)groups);
+#endif
+    return true;
+}
+
+struct Tile {
+    int n, m, q0;  // slab (n, m) and the first query (place in the query order) of this wave
+    int part;      // which of the p.k_split parts of the queries' samples this workgroup takes
+};
+
+// The work of wave `wave` of a workgroup that takes `chunk` of `slab`. The heads of one slab group share cache
+// lines, so the waves of a workgroup take the same queries of all of them.
+__host__ __device__ inline Tile wave_work(const Params& p, int ppw, int slab, int chunk, int wave) {
+    const int groups = p.M / p.head_group;
+    const int waves = p.q_per_block / ppw;  // waves per head
+    const int hg = wave / waves;
+    Tile t;
+    t.n = slab / groups;
+    t.m = (slab - t.n * groups) * p.head_group + hg;
+    t.part = 0;
+    if (p.k_split > 1) {
+        // the parts of one query chunk are consecutive work items
+        t.part = chunk % p.k_split;
+        chunk /= p.k_split;
+    }
+    t.q0 = chunk * p.q_per_block + (wave - hg * waves) * ppw;
+    return t;
+}
+
+// Launch shape of a gather kernel of `ppw` queries per wave: fills the arrangement fields of `p` for its
+// n_batch and k_split_max (host code).
+struct GatherLaunch {
+    int grid;   // workgroups (0: nothing to do)
+    int waves;  // waves per workgroup
+};
+GatherLaunch plan_gather(Params& p, int ppw, int elem_bytes);
 
 // The chunk ranges of the band arrangement (p.xcd_bands) for p.q_per_block queries per chunk: fills
 // p.band_c, p.band_count and p.band_cap from the level table (host code).
