@@ -969,8 +969,8 @@ __device__ __forceinline__ void flush_run(float4* acc, int key, int TH, int TW, 
 //      DETR, Swin and BEV shapes, against slices alone; units alone made the DETR backward 8 % slower.
 //   4. the tile's on-map pixels are stored once (plain stores), or added with atomics when the
 //      tile is split over several work items (its rows were zeroed before).
-// Every grad_out row read past a unit's or a slice's end uses an out-of-range buffer offset, which
-// returns zeros.
+// Every grad_out row read past a unit's or a slice's end, and by lanes past the last channel, uses an
+// out-of-range buffer offset (fold_nothing), which returns zeros.
 // DET: records ranked per key in load order (ballots instead of LDS atomics), and split tiles'
 // sums written to p.partials for split_reduce_kernel instead of added with atomics.
 template <typename T, bool DET>
@@ -986,9 +986,9 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     int4* srec = s_rec[wave];
     int* skey = s_key[wave];
     float4* acc = s_acc[wave];
+    const int D = p.D, nothing = fold_nothing(p);
     // places past a unit's or a slice's end read this record: no weight, and a row past grad_out's end
-    if (lane == 0) srec[kChunkRecords] = make_int4((int)kOOBElem, 0, 0, 0);
-    const int D = p.D;
+    if (lane == 0) srec[kChunkRecords] = make_int4(nothing, 0, 0, 0);
     const rsrc_t gr = make_rsrc(p.grad_out, (uint32_t)((size_t)p.n_batch * p.Lq * p.M * D * sizeof(T)));
     const int sub = lane % kLPR, grp = lane / kLPR;  // lane within its record stream, stream
     constexpr int kRecPerLane = kChunkRecords / 64;
@@ -1226,7 +1226,7 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         for (int ch0 = ch_first; ch0 < ch_end; ch0 += 4 * kPixQ) {
             // the lane's first channel, or past the end of every row; channels past D in its other float4s may
             // read the next row's, and their sums are never stored
-            const int ch = ch0 + 4 * kQPL * sub < D ? ch0 + 4 * kQPL * sub : (int)kOOBElem;
+            const int ch = ch0 + 4 * kQPL * sub < D ? ch0 + 4 * kQPL * sub : nothing;
             auto load_row = [&](float4 (&x)[kQPL], int row) {
                 const uint32_t off = (uint32_t)(row + ch);
 #pragma unroll
@@ -1483,7 +1483,7 @@ void pick_small_items(Params& p) {
 bool plan_binned(Params& p) {
     const bool runs = p.D % 4 == 0;  // the run fold: any D, 8 x 8 tiles, 32 channels at a time
     if ((!runs && p.D > kBinnedMaxD) || p.Lq == 0 || p.K > kCountQueries) return false;
-    // grad_out is read through a buffer resource whose out-of-range offset is kOOBElem
+    // grad_out is read through a buffer resource, and the offsets past its end stay below 2^32 bytes (fold_nothing)
     if ((int64_t)p.n_batch * p.Lq * p.M * p.D >= kMaxLaunchElems) return false;
     // largest square tile (2^e x 2^e pixels) whose accumulator, with its one-pixel margin, fits
     auto padded = [&](int eh, int ew) { return runs ? 0 : ((1 << eh) + 2) * ((1 << ew) + 2) * p.D; };

@@ -217,6 +217,11 @@ __host__ __device__ inline bool block_work(const Params& p, uint32_t b, uint32_t
     return true;
 }
 
+// Element offset that stands, in the fold, for a grad_out row that is not there and for channels past D: grad_out's
+// number of elements. A row and a channel of which one or both are this lie past grad_out's end, and below
+// 2^30 elements, so that their byte offset in 32 bits does not wrap round to its start.
+__host__ __device__ inline int fold_nothing(const Params& p) { return p.n_batch * p.Lq * p.M * p.D; }
+
 struct Tile {
     int n, m, q0;  // slab (n, m) and the first query (place in the query order) of this wave
     int part;      // which of the p.k_split parts of the queries' samples this workgroup takes

@@ -39,6 +39,27 @@ int main() {
                     }
                 }
         }
+    // the fold's rows and channels that are not there: past grad_out's end as 32-bit byte offsets, alone and together
+    // and at the second 16 bytes of a lane, up to the largest problem that the binned path takes
+    for (int64_t elems : {int64_t(4), int64_t(96), int64_t(1) << 20, (int64_t(1) << 28) + 36, msda::kMaxLaunchElems - 4}) {
+        msda::Params p = {};
+        p.n_batch = p.Lq = p.M = 1;
+        p.D = (int)elems;
+        const int64_t nothing = msda::fold_nothing(p);
+        for (int64_t row : {int64_t(0), elems - 4, nothing})
+            for (int64_t ch : {int64_t(0), int64_t(28), nothing})
+                for (int64_t more : {0, 4}) {
+                    if (row != nothing && ch != nothing) continue;
+                    for (int bytes : {2, 4}) {
+                        const uint32_t at = (uint32_t)(row + ch) * (uint32_t)bytes + (uint32_t)(more * bytes);
+                        if ((int64_t)at < elems * bytes) {
+                            ++failures;
+                            std::printf("fold marker: %lld elements, row %lld + channel %lld + %lld\n", (long long)elems,
+                                        (long long)row, (long long)ch, (long long)more);
+                        }
+                    }
+                }
+    }
     std::printf("failures: %d\n", failures);
     return failures != 0;
 }
