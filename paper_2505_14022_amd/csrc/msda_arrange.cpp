@@ -81,26 +81,28 @@ GatherLaunch plan_gather(Params& p, int ppw, int elem_bytes) {
     // in the backward; workgroups of 8 or 16 waves were slower.
     p.strip_rows = waves > 1 && xcd_split(p) && xcd_bands(p) && p.S < kStripMaxPixels ? kStripRows : 0;
     p.head_group = waves > 1 && p.M % 2 == 0 && p.D * elem_bytes == 64 ? 2 : 1;
-    p.q_per_block = waves * ppw / p.head_group;
+    p.groups = p.M / p.head_group;
+    p.n_groups = p.n_batch * p.groups;
+    p.head_waves = waves / p.head_group;
+    p.q_per_block = p.head_waves * ppw;
     const int qchunks = (p.Lq + p.q_per_block - 1) / p.q_per_block;
     // a grid too small to fill the chip splits each query's samples over up to k_split_max
     // work items, as long as a part keeps kSplitMinSamples samples
     int ks = 1;
     while (2 * ks <= p.k_split_max && 2 * ks * kSplitMinSamples <= p.K &&
-           (int64_t)p.n_batch * p.M * qchunks * (p.q_per_block / ppw) * 2 * ks <= kSplitWaves)
+           (int64_t)p.n_batch * p.M * qchunks * p.head_waves * 2 * ks <= kSplitWaves)
         ks *= 2;
     p.k_split = ks;
     p.chunks = qchunks * ks;
-    const int n_groups = p.n_batch * p.M / p.head_group;
-    p.num_blocks = n_groups * p.chunks;
+    p.num_blocks = p.n_groups * p.chunks;
     if (p.num_blocks == 0) return {0, waves};
-    const int64_t split_grid = 8 * (int64_t)n_groups * ((p.chunks + 7) / 8);
+    const int64_t split_grid = 8 * (int64_t)p.n_groups * ((p.chunks + 7) / 8);
     p.xcd_split = xcd_split(p) && split_grid <= INT32_MAX;
     p.xcd_bands = 0;
     int64_t band_grid = 0;
     if (p.xcd_split && ks == 1 && xcd_bands(p)) {
         set_bands(p);
-        band_grid = 8 * (int64_t)n_groups * p.band_cap;
+        band_grid = 8 * (int64_t)p.n_groups * p.band_cap;
         p.xcd_bands = band_grid <= INT32_MAX;
     }
     return {p.xcd_bands ? (int)band_grid : p.xcd_split ? (int)split_grid : (p.num_blocks + 7) / 8 * 8, waves};

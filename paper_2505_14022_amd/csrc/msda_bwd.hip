@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
 
     Tile t;
     if (!tile_of(p, PPW, t)) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = wave_index(), lane = threadIdx.x & 63;
     const int ps = lane / LPP, sub = lane % LPP;
     const int K = p.K;
     const int KC = K < kMaxItems / PPW ? K : kMaxItems / PPW;

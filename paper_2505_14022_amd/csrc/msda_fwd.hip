@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kBlock) void fwd_kernel(Params p) {
 
     Tile t;
     if (!tile_of(p, PPW, t)) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = wave_index(), lane = threadIdx.x & 63;
     const int ps = lane / LPP, sub = lane % LPP;
     if (lane < PPW) s_q[wave][lane] = query_at(p, s_lvl, t.q0 + lane);
     wave_lds_sync();

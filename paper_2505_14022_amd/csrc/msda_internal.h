@@ -113,6 +113,9 @@ struct Params {
     int chunks;            // work items per slab: ceil(Lq / q_per_block) * k_split
     int strip_rows;        // query order of the gather kernels: strips of this many rows (0: the query index)
     int head_group;        // heads that one workgroup of the gather kernels takes together (divides M)
+    int groups;            // M / head_group
+    int n_groups;          // n_batch * groups: slab groups
+    int head_waves;        // waves of a workgroup per head (head_group * head_waves waves in all)
     int k_split;           // bwd_kernel: a query chunk's samples are split over k_split work items
     int k_split_max;       // set by the launcher: the largest k_split it accepts (0 or 1: none)
     int xcd_split;         // forward / bwd_kernel work arrangement (tile_of): 1 query eighths, 0 slab ranges
@@ -177,7 +180,7 @@ __host__ __device__ inline bool block_work(const Params& p, uint32_t b, uint32_t
         const int x = (int)(b & 7u), i = (int)(b >> 3);
         slab = i / p.band_cap;
         int k = i - slab * p.band_cap;
-        if (slab >= p.n_batch * p.M / p.head_group || k >= p.band_count[x]) return false;
+        if (slab >= p.n_groups || k >= p.band_count[x]) return false;
         chunk = -1;
         for (int l = 0; l < p.L; ++l) {
             const int c0 = p.band_c[l][x], n = p.band_c[l][x + 1] - c0;
@@ -194,7 +197,7 @@ __host__ __device__ inline bool block_work(const Params& p, uint32_t b, uint32_t
         const int per = (p.chunks + 7) >> 3;
         slab = i / per;
         chunk = (int)(((int64_t)x * p.chunks) >> 3) + (i - slab * per);
-        return slab < p.n_batch * p.M / p.head_group && chunk < (int)(((int64_t)(x + 1) * p.chunks) >> 3);
+        return slab < p.n_groups && chunk < (int)(((int64_t)(x + 1) * p.chunks) >> 3);
     }
 #ifndef MSDA_ABLATE_NO_XCD_REMAP
     const uint32_t w = (b & 7u) * (G >> 3) + (b >> 3);
@@ -208,11 +211,10 @@ __host__ __device__ inline bool block_work(const Params& p, uint32_t b, uint32_t
     chunk = (int)(w - (uint32_t)slab * (uint32_t)p.chunks);
 #else
     // work items ordered (batch, query chunk, head group): the heads of one chunk are consecutive
-    const int groups = p.M / p.head_group;
-    const int nc = (int)(w / (uint32_t)groups);
+    const int nc = (int)(w / (uint32_t)p.groups);
     const int n = nc / p.chunks;
     chunk = nc - n * p.chunks;
-    slab = n * groups + (int)(w - (uint32_t)nc * (uint32_t)groups);
+    slab = n * p.groups + (int)(w - (uint32_t)nc * (uint32_t)p.groups);
 #endif
     return true;
 }
@@ -230,19 +232,17 @@ struct Tile {
 // The work of wave `wave` of a workgroup that takes `chunk` of `slab`. The heads of one slab group share cache
 // lines, so the waves of a workgroup take the same queries of all of them.
 __host__ __device__ inline Tile wave_work(const Params& p, int ppw, int slab, int chunk, int wave) {
-    const int groups = p.M / p.head_group;
-    const int waves = p.q_per_block / ppw;  // waves per head
-    const int hg = wave / waves;
+    const int hg = wave >= p.head_waves ? 1 : 0;  // head_group is 1 or 2
     Tile t;
-    t.n = slab / groups;
-    t.m = (slab - t.n * groups) * p.head_group + hg;
+    t.n = slab / p.groups;
+    t.m = (slab - t.n * p.groups) * p.head_group + hg;
     t.part = 0;
     if (p.k_split > 1) {
         // the parts of one query chunk are consecutive work items
         t.part = chunk % p.k_split;
         chunk /= p.k_split;
     }
-    t.q0 = chunk * p.q_per_block + (wave - hg * waves) * ppw;
+    t.q0 = chunk * p.q_per_block + (wave - hg * p.head_waves) * ppw;
     return t;
 }
 
