@@ -973,7 +973,12 @@ __device__ __forceinline__ void flush_run(float4* acc, int key, int TH, int TW, 
 // out-of-range buffer offset (fold_nothing), which returns zeros.
 // DET: records ranked per key in load order (ballots instead of LDS atomics), and split tiles'
 // sums written to p.partials for split_reduce_kernel instead of added with atomics.
-template <typename T, bool DET>
+// SLAB: the work items of bin_slab_kernel (p.slab_bins), each a word beside its tile's descriptor, taken in a fixed
+// order. A kernel of its own: as a branch at run time its divisions and its scalar registers (29 to 33 of the
+// deterministic kernel's spilled, 17 without) cost every other fold (4000 queries of 16 samples over
+// 32x32 + 16x16 at batch 2, deterministic: 155.3 us, 153.0 without; fp16 cross-attention, 12000 queries
+// at batch 4: 475 and 464 us).
+template <typename T, bool DET, bool SLAB>
 __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     __shared__ int s_geo[kGeo * kMaxLevels];
     __shared__ int s_start[kAccWaves][kRunKeys + 1];
@@ -999,33 +1004,33 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     // (2-4 us off the backward against dealing items x, x + 8, ...). Each counter has a 256-byte line of its
     // own: all waves taking items from one counter (or from counters sharing a line) serialize on
     // it, which cost the fold a quarter of its time. A wave whose queue has drained helps the others.
-    int total = p.slab_bins ? *p.scan_done : p.tile_chunks[p.n_tiles];
-    total = (total < 0 ? 0 : (total > p.max_items ? p.max_items : total)) * p.ch_blocks;
-    // With p.slab_bins there are a few items per wave at most, and the waves take every nwaves-th one: a
+    const int ch_blocks = SLAB ? p.ch_blocks : 1;
+    int total = SLAB ? *p.scan_done : p.tile_chunks[p.n_tiles];
+    total = (total < 0 ? 0 : (total > p.max_items ? p.max_items : total)) * ch_blocks;
+    // With SLAB there are a few items per wave at most, and the waves take every nwaves-th one: a
     // queue's atomics, and the visits to the drained queues at the end, would take longer than the sums.
-    const bool fixed = p.slab_bins != 0;
     const int nwaves = gridDim.x * kAccWaves;
-    int owner = fixed ? 0 : blockIdx.x & (kQueues - 1), visited = fixed ? kQueues - 1 : 0;
-    auto qbase = [&](int q) { return fixed ? 0 : (int)(((int64_t)total * q) / kQueues); };
-    auto owned = [&](int q) { return fixed ? total : qbase(q + 1) - qbase(q); };
+    int owner = SLAB ? 0 : blockIdx.x & (kQueues - 1), visited = SLAB ? kQueues - 1 : 0;
+    auto qbase = [&](int q) { return SLAB ? 0 : (int)(((int64_t)total * q) / kQueues); };
+    auto owned = [&](int q) { return SLAB ? total : qbase(q + 1) - qbase(q); };
     auto item_at = [&](int q, int s) { return qbase(q) + s; };
     auto counter = [&](int q) { return p.queue + q * kQueueStride; };
-    // descriptor of work item `it` (its block of channels is it % p.ch_blocks): lanes 0..15 hold its 16 words
+    // descriptor of work item `it` (its block of channels is it % ch_blocks): lanes 0..15 hold its 16 words
     // words of this wave's first 64 items, one per lane
     const int first = blockIdx.x * kAccWaves + wave;
     const int ahead = first + lane * nwaves;
-    const int words = fixed && ahead < total ? p.items[ahead / p.ch_blocks] : 0;
+    const int words = SLAB && ahead < total ? p.items[ahead / ch_blocks] : 0;
     auto load_desc = [&](int it) {
-        int row = it / p.ch_blocks, chunk = 0;
-        if (fixed) {
+        int row = it / ch_blocks, chunk = 0;
+        if constexpr (SLAB) {
             const int k = (it - first) / nwaves;
             const int word = k < 64 ? __builtin_amdgcn_readlane(words, k) : __builtin_amdgcn_readfirstlane(p.items[row]);
             row = word >> kItemChunkBits;
             chunk = word & ((1 << kItemChunkBits) - 1);
         }
         int v = lane < 16 ? p.item_desc[(size_t)row * 16 + lane] : 0;
-        if (fixed && lane == 0) v = chunk * p.item_records;
-        if (fixed && lane == 1) v = min((chunk + 1) * p.item_records, v);
+        if (SLAB && lane == 0) v = chunk * p.item_records;
+        if (SLAB && lane == 1) v = min((chunk + 1) * p.item_records, v);
         return v;
     };
     // the item's visible records, kRecPerLane per lane (all loads in flight together); rows past
@@ -1050,7 +1055,7 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         }
     };
     int taken = first;
-    if (!fixed && lane == 0) taken = atomicAdd(counter(owner), 1);
+    if (!SLAB && lane == 0) taken = atomicAdd(counter(owner), 1);
     int pf_item = -1, pf_dv = 0;  // the next item of this queue and its prefetched descriptor
     for (;;) {
         const int slot = __builtin_amdgcn_readfirstlane(taken);
@@ -1068,7 +1073,7 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         }
         const int item = item_at(owner, slot);
         // the next slot is taken now; it is needed only when this item is done
-        if (fixed) taken = slot + nwaves;
+        if (SLAB) taken = slot + nwaves;
         else if (lane == 0) taken = atomicAdd(counter(owner), 1);
         const int dv = item == pf_item ? pf_dv : load_desc(item);
         int4 rc[kRecPerLane];
@@ -1220,9 +1225,9 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         const int lo = (C * grp) / kGroups, hi = (C * (grp + 1)) / kGroups;
         const int span = (C + kGroups - 1) / kGroups;
         const int key_lo = !by_units && hi > lo ? skey[lo] : 0;  // key of the slice's first record
-        // every channel, or with p.ch_blocks > 1 the item's block of them
-        const int ch_first = p.ch_blocks > 1 ? item % p.ch_blocks * (4 * kPixQ) : 0;
-        const int ch_end = p.ch_blocks > 1 ? min(ch_first + 4 * kPixQ, D) : D;
+        // every channel, or with SLAB the item's block of them
+        const int ch_first = SLAB ? item % ch_blocks * (4 * kPixQ) : 0;
+        const int ch_end = SLAB ? min(ch_first + 4 * kPixQ, D) : D;
         for (int ch0 = ch_first; ch0 < ch_end; ch0 += 4 * kPixQ) {
             // the lane's first channel, or past the end of every row; channels past D in its other float4s may
             // read the next row's, and their sums are never stored
@@ -1700,11 +1705,14 @@ hipError_t launch_fold_runs(const Params& p, msda_dtype_t dtype, hipStream_t str
     if (grid <= 0) return hipErrorInvalidConfiguration;
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, p); };
     if (p.deterministic) {
-        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, true>);
-        else go(fold_runs_kernel<float, true>);
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, true, false>);
+        else go(fold_runs_kernel<float, true, false>);
+    } else if (p.slab_bins) {
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false, true>);
+        else go(fold_runs_kernel<float, false, true>);
     } else {
-        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false>);
-        else go(fold_runs_kernel<float, false>);
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false, false>);
+        else go(fold_runs_kernel<float, false, false>);
     }
     return hipGetLastError();
 }
