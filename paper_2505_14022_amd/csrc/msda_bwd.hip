@@ -55,8 +55,17 @@ __device__ __forceinline__ void store_corner_sums(float (&G)[4], int sub, int4* 
     }
 }
 
+// Waves per SIMD that bwd_kernel may hold: seven with fp16 rows, although its registers allow eight. Beside it, on
+// the other stream, the counting pass waits for room with a slab's histogram in LDS (22 KB at the
+// Swin-feature shape), and eight waves of it left none until it had finished: the pass took 300 us of the
+// backward instead of 112, the step 981 us instead of 952. With fp32 rows eight are as fast or faster
+// (DETR-encoder step 395 us, 398 with seven).
+template <typename T, bool ATOMIC>
+constexpr int kBwdWaves = sizeof(T) == 2 && !ATOMIC ? 7 : 8;
+
 template <typename T, int VEC, int LPP, bool ATOMIC>
-__global__ __launch_bounds__(kBlock) void bwd_kernel(Params p) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, (kBwdWaves<T, ATOMIC>))))
+void bwd_kernel(Params p) {
     constexpr int PPW = 64 / LPP;
     __shared__ int s_lvl[3 * kMaxLevels];
     __shared__ int4 s_off[kWaves][kMaxItems];

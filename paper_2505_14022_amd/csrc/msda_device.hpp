@@ -253,7 +253,7 @@ __device__ __forceinline__ float2 group_softmax_stats(float z, int G) {
 
 // The wave's place in its workgroup, as a scalar: from threadIdx alone the compiler keeps it, and the head, the first
 // query and the LDS addresses that follow from it, in vector registers. Those took the fp32 forward and the
-// fp16 bwd_kernel from 8 to 7 waves per SIMD (66 and 68 registers; 62 and 62 so).
+// fp16 bwd_kernel from 62 to 66 and 68 registers, past the 64 of eight waves per SIMD.
 __device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
 // The work of this wave (false: none).
