@@ -264,18 +264,18 @@ __device__ __forceinline__ bool tile_of(const Params& p, int PPW, Tile& t) {
     return true;
 }
 
-// The query at place i of the query order: the query index, or with p.strip_rows (self-attention over
-// the maps) strips of that many rows, so that consecutive places are a compact patch of the level
+// The query at place i of the query order: the query index, or with p.strips (self-attention over
+// the maps) strips of at most kStripRows rows, so that consecutive places are a compact patch of the level
 // and the queries of a CU's waves read fewer distinct rows: the fp16 gathers are bound by the vector
 // cache's misses. Read requests to L2 per forward call: Swin-feature shape 33 -> 20 M, DETR-encoder
 // shape 9.4 -> 6.1 M. Places past Lq stay past Lq.
 __device__ __forceinline__ int query_at(const Params& p, const int* s_lvl, int i) {
-    if (!p.strip_rows || i >= p.Lq) return i;
+    if (!p.strips || i >= p.Lq) return i;
     int l = 0;
     for (int j = 1; j < p.L; ++j)
         if (i >= p.start[j]) l = j;
     const int st = s_lvl[2 * kMaxLevels + l];
-    return st + strip_pixel(i - st, s_lvl[l], s_lvl[kMaxLevels + l], p.strip_rows);
+    return st + strip_pixel(i - st, s_lvl[l], s_lvl[kMaxLevels + l]);
 }
 
 // The level of sample k of a query.

@@ -8,19 +8,26 @@
 
 int main() {
     int failures = 0;
-    // strip_pixel is a permutation of a level's pixels, and every run of strip * n places that starts at a
-    // strip's column covers n whole columns of the strip
-    for (int H : {1, 2, 7, 8, 9, 15, 16, 23, 100, 1000})
+    // strip_pixel is a permutation of a level's pixels that keeps every eighth of the rows (the band that one XCD
+    // takes, as set_bands cuts the levels) in its own places, and that runs over an eighth in strips of at most
+    // kStripRows rows, column by column
+    for (int H : {1, 2, 7, 8, 9, 13, 15, 16, 23, 25, 38, 50, 100, 151, 1000})
         for (int W : {1, 2, 5, 8, 33, 1048}) {
             if ((int64_t)H * W >= msda::kStripMaxPixels) continue;
-            const int strip = msda::kStripRows;
             std::vector<int> seen(H * W, 0);
             bool ok = true;
+            int prev = -1;  // the pixel before
             for (int r = 0; r < H * W; ++r) {
-                const int px = msda::strip_pixel(r, H, W, strip);
+                const int px = msda::strip_pixel(r, H, W);
                 ok = ok && px >= 0 && px < H * W && ++seen[px] == 1;
-                const int s = r / (strip * W), top = s * strip, rows = H - top < strip ? H - top : strip;
-                ok = ok && px / W >= top && px / W < top + rows && px % W == (r - top * W) / rows;
+                auto band = [&](int row) { return (8 * row + 4) / H; };
+                ok = ok && band(px / W) == band(r / W);
+                if (prev >= 0) {  // one row down, or to the strip's top row one column on, or to a new strip's first column
+                    const int dr = px / W - prev / W, dc = px % W - prev % W;
+                    const bool down = dr == 1 && dc == 0, on = dc == 1 && dr <= 0 && -dr < msda::kStripRows;
+                    ok = ok && (down || on || px % W == 0);
+                }
+                prev = px;
             }
             if (!ok) {
                 ++failures;
