@@ -79,7 +79,7 @@ GatherLaunch plan_gather(Params& p, int ppw, int elem_bytes) {
     // DETR-encoder fp32 91 / 300 -> 89 / 293 (its 128-byte rows hit the cache more often, and its
     // loads run at 0.7 of the cache's rate). Strips of 16 rows were 2-5 % slower, of 4 rows 1-15 %
     // in the backward; workgroups of 8 or 16 waves were slower.
-    p.strips = waves > 1 && xcd_split(p) && xcd_bands(p) && p.S < kStripMaxPixels;
+    p.strips = waves > 1 && p.Lq == p.S && p.S < kStripMaxPixels;
     for (int l = 0; l < p.L; ++l)
         if (p.H[l] > kStripMaxRows) p.strips = 0;
     p.head_group = waves > 1 && p.M % 2 == 0 && p.D * elem_bytes == 64 ? 2 : 1;

@@ -9,6 +9,8 @@
 // Ablation builds (never the product library): each MSDA_ABLATE_* macro, set on the compiler
 // command line by microbench/ablation.py, replaces one design choice with a complete, correct
 // alternative, so that the choice can be timed and counted against the product build.
+// The query order (strips) and the head pairs are those of the product in all of them but LDS_STAGE, whose
+// forward takes one head and the query index where a level is staged.
 //   MSDA_ABLATE_NO_XCD_REMAP    workgroup b runs work item b on every shape (no XCD-aware arrangement)
 //   MSDA_ABLATE_HEAD_FASTEST    work items in (batch, query chunk, head) order instead of slab-major
 //                               (slab ranges on every shape)
@@ -85,7 +87,8 @@ __host__ __device__ inline float fast_rcp(float x) {
 // in strips of rows, as few of equal height as leave at most kStripRows rows a strip, and column by column within
 // a strip. Cutting the strips at the bands keeps an XCD's queries in its rows: with strips of 8 rows across the
 // bands, 79, 56, 39 and 23 % of the queries of the four DETR levels were in their XCD's band (99, 97, 86 and
-// 47 % in index order), and the DETR-encoder forward moved 203 MB and bwd_kernel 271; 186 and 253 so, with the same requests to L2.
+// 47 % in index order), and the DETR-encoder forward moved 203 MB and bwd_kernel 271; 186 and 253 so, with the
+// same requests to L2.
 __host__ __device__ inline int strip_pixel(int r, int H, int W) {
     const int h = small_div(r, fast_rcp((float)W));               // the row that place r has in row-major order,
     const int x = small_div(8 * h + 4, fast_rcp((float)H));       // and the band, whose rows have the same places

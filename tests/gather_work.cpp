@@ -35,6 +35,12 @@ void check(const Case& c, int ppw, int k_split_max) {
     }
     p.Lq = c.Lq ? c.Lq : p.S;
     const msda::GatherLaunch g = msda::plan_gather(p, ppw, c.elem);
+    // the query order and the head pairs do not depend on the arrangement
+    const bool pairs = g.waves > 1 && c.M % 2 == 0 && c.D * c.elem == 64, strips = g.waves > 1 && p.Lq == p.S;
+    if ((p.head_group == 2) != pairs || (p.strips != 0) != strips) {
+        ++failures;
+        std::printf("%s: strips %d, head group %d\n", c.name, p.strips, p.head_group);
+    }
     std::vector<int> times((size_t)c.N * c.M * p.Lq * p.k_split, 0);
     int64_t outside = 0, wrong = 0;
     for (int b = 0; b < g.grid; ++b) {
