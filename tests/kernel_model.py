@@ -7,11 +7,15 @@ code launches it and as each lane forms its addresses:
   * the host's batch split (largest batch count per launch that keeps element offsets below
     2^29) and the launch geometry (channels per lane, lanes per query, queries per wave, grid
     padded to a multiple of 8);
-  * the workgroup -> (batch, head, query chunk) arrangement over the eight XCDs: query eighths
+  * the workgroup -> (batch, heads, query chunk) arrangement over the eight XCDs: query eighths
     (XCD x takes the x-th eighth of every slab's query chunks) when there are at least half as many
     queries as value pixels, else slab ranges (XCD x takes a contiguous eighth of the slab-major
     work items); with as many queries as value pixels the eighths are bands of rows (XCD x takes
     the chunks whose first query lies in the x-th eighth of the rows of its level);
+  * two heads per four-wave workgroup where two heads' rows of a pixel are one 128-byte line (half of
+    the waves each, on the same queries), and the query order of self-attention over the maps (as
+    many queries as value pixels, four-wave workgroups): within each eighth of a level's rows, strips of
+    at most 8 rows, column by column;
   * the sample split of small grids: a query chunk's K samples divided over up to 8 consecutive
     work items (at least 4 samples each, at most 4096 waves in all);
   * the per-sample description: fp32 image coordinates, the open range test, floor, the int32
@@ -40,6 +44,9 @@ ATOMIC_ROW_FLOATS = 512  # grad_out floats of one wave staged for the row-coales
 K_SPLIT_MAX = 8          # most parts the backward splits a query chunk's samples into ...
 K_SPLIT_MIN_SAMPLES = 4  # ... keeping at least this many samples per part ...
 K_SPLIT_WAVES = 4096     # ... while the grid stays within this many waves
+STRIP_ROWS = 8           # most rows of a strip of the query order ...
+STRIP_MAX_PIXELS = 1 << 20  # ... which maps of this many pixels ...
+STRIP_MAX_ROWS = 1 << 17    # ... or of more rows than this do not take
 U32 = 1 << 32
 
 
@@ -92,6 +99,8 @@ class Launch:
     grid: int
     split: bool
     k_split: int
+    head_group: int = 1     # heads per workgroup
+    order: np.ndarray = None  # query at each place of the query order (None: the query index)
     bands: bool = False
     band_c: tuple = ()      # band_c[l][x]: first chunk of level l in band x (x = 0..8)
     band_count: tuple = ()  # chunks of one slab in band x
@@ -110,13 +119,34 @@ def band_table(shapes, qpb):
     for H, W in shapes:
         row = []
         for x in range(8):
-            r0 = max(0, -(-(x * H - 4) // 8))  # first row with 8 h + 4 >= x H
-            row.append(first_chunk(start + r0 * W))
+            row.append(first_chunk(start + first_row(H, x) * W))
         start += H * W
         row.append(first_chunk(start))
         bc.append(tuple(row))
     count = tuple(sum(r[x + 1] - r[x] for r in bc) for x in range(8))
     return tuple(bc), count, max(count)
+
+
+def first_row(H, x):
+    """The first row of band x of a level of H rows: 8 h + 4 >= x H."""
+    return max(0, -(-(x * H - 4) // 8))
+
+
+def strip_order(shapes):
+    """The query order of self-attention over the maps, listed strip by strip: each band of rows in as few
+    strips of equal height as leave at most STRIP_ROWS rows a strip (the last has the rows that are left)."""
+    order, start = [], 0
+    for H, W in shapes:
+        for x in range(8):
+            top, end = first_row(H, x), first_row(H, x + 1)
+            if end > top:
+                strips = -(-(end - top) // STRIP_ROWS)
+                high = -(-(end - top) // strips)
+                for r in range(top, end, high):
+                    rows = np.arange(r, min(r + high, end))
+                    order.append((start + rows[None, :] * W + np.arange(W)[:, None]).ravel())
+        start += H * W
+    return np.concatenate(order)
 
 
 def launches(N, S, M, D, Lq, L, P, es, shapes=None):
@@ -130,23 +160,27 @@ def launches(N, S, M, D, Lq, L, P, es, shapes=None):
         cnt = min(nb, N - n0)
         chunks4 = (Lq + WAVES_PER_BLOCK * ppw - 1) // (WAVES_PER_BLOCK * ppw)
         waves = 1 if cnt * M * chunks4 < SMALL_GRID else WAVES_PER_BLOCK
-        qpb = waves * ppw
+        hg = 2 if waves > 1 and M % 2 == 0 and D * es == 64 else 1
+        qpb = waves // hg * ppw
         qchunks = (Lq + qpb - 1) // qpb
         ks = 1
         while (2 * ks <= K_SPLIT_MAX and 2 * ks * K_SPLIT_MIN_SAMPLES <= L * P and
-               cnt * M * qchunks * waves * 2 * ks <= K_SPLIT_WAVES):
+               cnt * M * qchunks * (waves // hg) * 2 * ks <= K_SPLIT_WAVES):
             ks *= 2
         chunks = qchunks * ks
-        num_blocks = cnt * M * chunks
-        split_grid = 8 * cnt * M * ((chunks + 7) // 8)
+        groups = cnt * M // hg
+        num_blocks = groups * chunks
+        split_grid = 8 * groups * ((chunks + 7) // 8)
         split = 2 * Lq >= S and split_grid <= MAX_INDEX
         grid = split_grid if split else (num_blocks + 7) // 8 * 8
-        ln = Launch(n0, cnt, vec, lpp, ppw, waves, qpb, chunks, num_blocks, grid, split, ks)
+        ln = Launch(n0, cnt, vec, lpp, ppw, waves, qpb, chunks, num_blocks, grid, split, ks, hg)
+        if Lq == S and shapes is None:
+            raise ValueError("self-attention over the maps needs the level shapes")
+        if waves > 1 and Lq == S and S < STRIP_MAX_PIXELS and all(h <= STRIP_MAX_ROWS for h, _ in shapes):
+            ln.order = strip_order(shapes)
         if split and ks == 1 and Lq == S:
-            if shapes is None:
-                raise ValueError("the band arrangement needs the level shapes")
             bc, count, cap = band_table(shapes, qpb)
-            band_grid = 8 * cnt * M * cap
+            band_grid = 8 * groups * cap
             if band_grid <= MAX_INDEX:
                 ln.bands, ln.band_c, ln.band_count, ln.band_cap, ln.grid = True, bc, count, cap, band_grid
         out.append(ln)
@@ -163,13 +197,16 @@ def wave_queries(ln: Launch, M: int):
     with x = b % 8 and i = b / 8, workgroup b runs the (i % cap)-th chunk of band x of slab i / cap
     (bands of rows: the chunks of band x, level after level), chunk x*chunks/8 + i % per of slab
     i / per (query eighths, per = ceil(chunks / 8)) or work item w = x * (G / 8) + i in slab-major
-    order (slab ranges). Every (slab, chunk) must be run exactly once; a work item is query chunk
-    chunk / k_split, sample part chunk % k_split."""
+    order (slab ranges). A slab is head_group heads of a batch item here. Every (slab, chunk) must be run
+    exactly once; a work item is query chunk chunk / k_split, sample part chunk % k_split, and the places
+    of its queries are read through the query order."""
+    hg = ln.head_group
+    groups = M // hg
     b = np.arange(ln.grid, dtype=np.int64)
     x, i = b & 7, b >> 3
     if ln.bands:
         slab, k = i // ln.band_cap, i % ln.band_cap
-        keep = (slab < ln.cnt * M) & (k < np.asarray(ln.band_count)[x])
+        keep = (slab < ln.cnt * groups) & (k < np.asarray(ln.band_count)[x])
         slab, k, xs = slab[keep], k[keep], x[keep]
         chunk = np.full(slab.shape, -1, dtype=np.int64)
         for l, row in enumerate(ln.band_c):
@@ -183,7 +220,7 @@ def wave_queries(ln: Launch, M: int):
         per = (ln.chunks + 7) // 8
         slab = i // per
         chunk = ((x * ln.chunks) >> 3) + i % per
-        keep = (slab < ln.cnt * M) & (chunk < (((x + 1) * ln.chunks) >> 3))
+        keep = (slab < ln.cnt * groups) & (chunk < (((x + 1) * ln.chunks) >> 3))
         slab, chunk = slab[keep], chunk[keep]
     else:
         w = x * (ln.grid >> 3) + i
@@ -194,14 +231,18 @@ def wave_queries(ln: Launch, M: int):
     _check((chunk >= 0) & (chunk < ln.chunks), "work item chunk out of range")
     _check((np.unique(item).size == item.size) & (item.size == ln.num_blocks),
            "work items not covered exactly once")
-    n, m = slab // M, slab % M
     part, qchunk = chunk % ln.k_split, chunk // ln.k_split
     wave = np.arange(ln.waves, dtype=np.int64)
     ps = np.arange(ln.ppw, dtype=np.int64)
-    q = (qchunk[:, None, None] * ln.q_per_block + wave[None, :, None] * ln.ppw + ps[None, None, :])
+    head_waves = ln.waves // hg
+    q = (qchunk[:, None, None] * ln.q_per_block + (wave % head_waves)[None, :, None] * ln.ppw + ps[None, None, :])
     shp = q.shape
     bc = lambda a: np.broadcast_to(a[:, None, None], shp).ravel()
-    return bc(n), bc(m), q.ravel(), bc(part)
+    m = (slab % groups)[:, None, None] * hg + (wave // head_waves)[None, :, None]
+    q = q.ravel()
+    if ln.order is not None:
+        q = np.where(q < ln.order.size, ln.order[np.minimum(q, ln.order.size - 1)], q)
+    return bc(slab // groups), np.broadcast_to(m, shp).ravel(), q, bc(part)
 
 
 def coalesced_atomics(D: int, vec: int, lpp: int) -> bool:

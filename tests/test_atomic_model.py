@@ -35,6 +35,14 @@ BANDS = [
     (1, 8, 32, ((33, 17), (9, 9)), 2, 33 * 17 + 81, "f16"),
 ]
 
+# four-wave workgroups of two heads each (64-byte rows): in the query order of bands of rows, in query eighths and
+# in slab ranges
+PAIRS = [
+    (2, 8, 32, ((56, 60), (28, 30), (5, 9)), 1, 56 * 60 + 28 * 30 + 5 * 9, "f16"),
+    (2, 8, 16, ((90, 91),), 2, 5001, "f32"),
+    (3, 6, 32, ((90, 91),), 2, 4001, "f16"),
+]
+
 
 def _compare(inp):
     gv, stats = model_atomic_backward(inp.value, inp.shapes, inp.starts, inp.loc, inp.attn, inp.grad_out)
@@ -47,7 +55,7 @@ def _compare(inp):
     return stats
 
 
-@pytest.mark.parametrize("case", SMALL + BANDS, ids=lambda c: f"N{c[0]}M{c[1]}D{c[2]}L{len(c[3])}P{c[4]}Lq{c[5]}{c[6]}")
+@pytest.mark.parametrize("case", SMALL + BANDS + PAIRS, ids=lambda c: f"N{c[0]}M{c[1]}D{c[2]}L{len(c[3])}P{c[4]}Lq{c[5]}{c[6]}")
 def test_small_cases(case):
     N, M, D, shapes, P, Lq, dt = case
     _compare(workloads.random_case(N, M, D, shapes, P, Lq, dt, seed=1000 + D + Lq))
@@ -113,6 +121,49 @@ def test_band_table_partitions_the_chunks():
         chunks = [c for row in bc for x in range(8) for c in range(row[x], row[x + 1])]
         assert sorted(chunks) == list(range((S + qpb - 1) // qpb))
         assert sum(count) == len(chunks) and cap == max(count)
+
+
+def _launch(c):
+    from kernel_model import launches
+
+    N, M, D, shapes, P, Lq, dt = c
+    ln, = launches(N, sum(h * w for h, w in shapes), M, D, Lq, len(shapes), P, 2 if dt == "f16" else 4, shapes=shapes)
+    return ln
+
+
+def test_head_pairs_and_query_order_are_modelled():
+    assert [_launch(c).head_group for c in PAIRS] == [2, 2, 2]
+    assert [_arrangements(*c) for c in PAIRS] == [{"bands"}, {"eighths"}, {"slabs"}]
+    assert [_launch(c).order is not None for c in PAIRS] == [True, False, False]
+
+
+def _share_in_band(ln, M, shapes):
+    """Per level, the share of its queries that the XCD of their band of rows takes (bands of rows)."""
+    from kernel_model import wave_queries
+
+    _, _, q, _ = wave_queries(ln, M)
+    b = np.arange(ln.grid)
+    x, i = b & 7, b >> 3
+    work = (i // ln.band_cap < ln.num_blocks // ln.chunks) & (i % ln.band_cap < np.asarray(ln.band_count)[x])
+    x = np.repeat(x[work], ln.waves * ln.ppw)
+    shares, start = [], 0
+    for H, W in shapes:
+        mine = (q >= start) & (q < start + H * W)
+        shares.append(np.mean((8 * ((q[mine] - start) // W) + 4) // H == x[mine]))
+        start += H * W
+    return np.array(shares)
+
+
+@pytest.mark.parametrize("name", ["detr_encoder", "swin5_f16", "bev_tsa_f16"])
+def test_an_xcds_queries_are_in_its_rows(name):
+    # A chunk goes with the band of its first query, so the last chunk of a band takes some queries of the next one.
+    # The query order keeps every band's pixels in the band's places, and so every share.
+    w = workloads.BY_NAME[name]
+    ln = _launch((w.N, w.M, w.D, w.shapes, w.P, w.Lq, w.dtype))
+    strips = _share_in_band(ln, w.M, w.shapes)
+    ln.order = None
+    rows = _share_in_band(ln, w.M, w.shapes)
+    assert np.array_equal(strips, rows) and rows[0] > 0.99
 
 
 def test_small_grids_split_samples():

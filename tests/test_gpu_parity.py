@@ -13,6 +13,11 @@ from gpu_util import check_parity, normwise, require_gpu, run_gpu, run_oracle, s
 
 pytestmark = pytest.mark.gpu
 
+# Problems of up to this many samples per level of a (batch item, head) are binned in one launch on the call's
+# own stream (and up to 2^21 samples in all). With more, the owner-computes backward takes the many-workgroup
+# passes on the forked stream.
+ONE_LAUNCH_SAMPLES = 16384
+
 
 @pytest.fixture(scope="module", autouse=True)
 def gpu():
@@ -85,25 +90,31 @@ def test_dense_coarse_levels_split_tiles(seed):
     check_parity(inp, workspace="owner")
 
 
-def test_many_tiles_multi_pass_scan():
-    # 128 slabs x 525 tiles: the bin scan runs over more than 256 workgroups (the last one scans
-    # their totals in several passes), and most of the scatter's workgroups only prepare work items
-    inp = workloads.random_case(16, 8, 4, ((168, 200),), 2, 48, "f32", seed=77)
+@pytest.mark.parametrize("Lq", [48, 8200])
+def test_many_tiles_multi_pass_scan(Lq):
+    # 128 slabs x 525 tiles. 8200 queries: the bin scan runs over more than 256 workgroups (the last one scans
+    # their totals in several passes), and most of the scatter's workgroups only prepare work items.
+    # 48 queries are binned in one launch, most of its work items without a record.
+    assert (2 * Lq > ONE_LAUNCH_SAMPLES) == (Lq == 8200)
+    inp = workloads.random_case(16, 8, 4, ((168, 200),), 2, Lq, "f32", seed=77)
     say("many tiles: multi-pass scan of workgroup totals")
     check_parity(inp, workspace="owner")
 
 
-def _hot_cell_case(n_hot: int, n_spread: int, seed: int):
-    """One 8 x 8 map (one fold tile per slab, one work item): n_hot samples of each slab fall in one
-    pixel cell (one key), the other n_spread are spread over the whole map."""
-    P, Lq = 4, (n_hot + n_spread) // 4
+def _hot_cell_case(n_hot: int, n_spread: int, seed: int, n_off: int = 0):
+    """One 8 x 8 map (one fold tile per slab): n_hot samples of each slab fall in one pixel cell (one key),
+    n_spread are spread over the whole map, and n_off lie off the map. With n_off > ONE_LAUNCH_SAMPLES the
+    samples on the map are one work item; without, there is one for every 64."""
+    P, Lq = 4, (n_hot + n_spread + n_off) // 4
     inp = workloads.random_case(1, 2, 32, ((8, 8),), P, Lq, "f32", seed=seed)
     rng = np.random.default_rng(seed)
     loc = inp.loc.reshape(1, Lq, 2, P, 2)
     for m in range(2):
         flat = loc[0, :, m].reshape(-1, 2)  # (q, p) order
         flat[:] = rng.uniform(0.02, 0.98, size=flat.shape).astype(np.float32)
-        hot = rng.choice(flat.shape[0], size=n_hot, replace=False)
+        places = rng.permutation(flat.shape[0]) if n_off else rng.choice(flat.shape[0], size=n_hot, replace=False)
+        hot = places[:n_hot]
+        flat[places[n_hot + n_spread:]] = np.float32(-0.5)
         # h_im in (3.1, 3.9), w_im in (4.1, 4.9): the cell whose top-left corner is pixel (3, 4)
         flat[hot, 0] = ((rng.uniform(4.1, 4.9, size=n_hot) + 0.5) / 8).astype(np.float32)
         flat[hot, 1] = ((rng.uniform(3.1, 3.9, size=n_hot) + 0.5) / 8).astype(np.float32)
@@ -111,13 +122,16 @@ def _hot_cell_case(n_hot: int, n_spread: int, seed: int):
     return inp
 
 
+@pytest.mark.parametrize("n_off", [0, 16400])
 @pytest.mark.parametrize("n_hot,n_spread", [(200, 300), (352, 148), (480, 20)])
-def test_fold_hot_key(n_hot, n_spread):
+def test_fold_hot_key(n_hot, n_spread, n_off):
+    # with the samples off the map, too many for the one-launch binning, an item is 512 records:
     # (200, 300) and (352, 148): runs average under 12 records, so the item is summed by work units,
     # and the hot key's 25 or 44 pieces fill whole rounds that add in up to 16 passes by rank;
     # (480, 20): the slice walk, with most slices ending on the hot key
-    inp = _hot_cell_case(n_hot, n_spread, seed=900 + n_hot)
-    say(f"fold hot key: {n_hot} samples in one cell, {n_spread} spread")
+    assert n_off == 0 or n_off > ONE_LAUNCH_SAMPLES
+    inp = _hot_cell_case(n_hot, n_spread, seed=900 + n_hot, n_off=n_off)
+    say(f"fold hot key: {n_hot} samples in one cell, {n_spread} spread, {n_off} off the map")
     check_parity(inp, workspace="owner")
 
 
@@ -236,12 +250,15 @@ def test_side_stream():
     assert normwise(gv.cpu().numpy(), ref["grad_value"]) <= 1e-4
 
 
-def test_backward_on_two_user_streams():
+@pytest.mark.parametrize("Lq", [2000, 4200])
+def test_backward_on_two_user_streams(Lq):
     # the owner-computes backward forks its grad_value work onto a library stream and joins it
-    # back; calls on two user streams from one thread must each see their own inputs
+    # back (4200 queries; 2000 stay on the call's stream); calls on two user streams from one thread
+    # must each see their own inputs
     import torch
 
-    cases = [workloads.random_case(1, 4, 32, ((24, 20), (12, 10)), 4, 2000, "f32", seed=20 + i) for i in range(2)]
+    assert (4 * Lq > ONE_LAUNCH_SAMPLES) == (Lq == 4200)
+    cases = [workloads.random_case(1, 4, 32, ((24, 20), (12, 10)), 4, Lq, "f32", seed=20 + i) for i in range(2)]
     say("backward on two user streams")
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     dev = [to_device(c) for c in cases]
@@ -259,19 +276,21 @@ def test_backward_on_two_user_streams():
         assert normwise(r[2].cpu().numpy(), ref["grad_attn"]) <= 1e-3
 
 
-def test_backward_graph_replays():
-    # forward + backward captured into a graph (the grad_value fork and join included), replayed
-    # several times with eager work in between; every replay must match the eager results
+@pytest.mark.parametrize("Lq", [1500, 4200])
+def test_backward_graph_replays(Lq):
+    # forward + backward captured into a graph (4200 queries: the grad_value fork and join included),
+    # replayed several times with eager work in between; every replay must match the eager results
     import torch
 
-    inp = workloads.random_case(2, 4, 32, ((24, 20), (12, 10)), 4, 1500, "f32", seed=31)
+    assert (4 * Lq > ONE_LAUNCH_SAMPLES) == (Lq == 4200)
+    inp = workloads.random_case(2, 4, 32, ((24, 20), (12, 10)), 4, Lq, "f32", seed=31)
     d = to_device(inp)
     say("graph capture and replays of forward + backward")
     w = inp.w
     ws = torch.empty(msda.workspace_size(inp.shapes, inp.starts, w.N, w.S, w.M, w.D, w.Lq, w.L, w.P, msda.MSDA_F32,
                                          msda.MSDA_WORKSPACE_OWNER),
                      dtype=torch.uint8, device="cuda")
-    out = torch.empty((2, 1500, 128), device="cuda")
+    out = torch.empty((2, Lq, 128), device="cuda")
     gv = torch.empty(tuple(inp.value.shape), device="cuda")
     gl = torch.empty(tuple(inp.loc.shape), device="cuda")
     ga = torch.empty(tuple(inp.attn.shape), device="cuda")
@@ -325,12 +344,13 @@ def _segment_stream(torch, ptr):
     return None
 
 
-def test_binding_allocates_on_the_call_stream():
+@pytest.mark.parametrize("Lq", [2000, 4200])
+def test_binding_allocates_on_the_call_stream(Lq):
     # outputs and workspaces the binding allocates belong to the stream the kernels run on, so the
     # caching allocator cannot hand them to other work while the call is still running there
     import torch
 
-    inp = workloads.random_case(1, 4, 32, ((24, 20), (12, 10)), 4, 2000, "f32", seed=41)
+    inp = workloads.random_case(1, 4, 32, ((24, 20), (12, 10)), 4, Lq, "f32", seed=41)
     d = to_device(inp)
     say("binding allocations on a stream other than the current one")
     s = torch.cuda.Stream()
@@ -350,8 +370,11 @@ def test_binding_allocates_on_the_call_stream():
                            "grad_loc": gl.cpu().numpy(), "grad_attn": ga.cpu().numpy()})
 
 
-def test_release_and_recreate_side_streams():
-    inp = workloads.random_case(1, 4, 32, ((24, 20), (12, 10)), 4, 2000, "f32", seed=42)
+@pytest.mark.parametrize("Lq", [2000, 4200])
+def test_release_and_recreate_side_streams(Lq):
+    # 4200 queries take the library's side stream, 2000 do without it
+    assert (4 * Lq > ONE_LAUNCH_SAMPLES) == (Lq == 4200)
+    inp = workloads.random_case(1, 4, 32, ((24, 20), (12, 10)), 4, Lq, "f32", seed=42)
     say("msda_release between backward calls")
     a = run_gpu(inp, workspace="owner")
     msda.release()

@@ -18,6 +18,9 @@ CASES = [
     (1, 1, 4, tuple((k + 1, 16 - k) for k in range(16)), 2, 700, "f32"),
     (3, 5, 48, ((31, 23), (16, 12), (8, 6)), 3, 999, "f16"),
     (1, 1, 32, ((120, 200),), 4, 4000, "f32"),                  # 375 tiles, few samples each
+    # 69632 one-pixel tiles in two blocks of channels: 68 work items for each of 2048 waves, the last four past
+    # the words that a wave holds ahead
+    (544, 8, 36, ((1, 1),) * 16, 1, 2, "f32"),
 ]
 
 
