@@ -977,8 +977,9 @@ __device__ __forceinline__ void flush_run(float4* acc, int key, int TH, int TW, 
 // order. A kernel of its own: as a branch at run time its divisions and its scalar registers (29 to 33 of the
 // deterministic kernel's spilled, 17 without) cost every other fold (4000 queries of 16 samples over
 // 32x32 + 16x16 at batch 2, deterministic: 155.3 us, 153.0 without; fp16 cross-attention, 12000 queries
-// at batch 4: 475 and 464 us).
-template <typename T, bool DET, bool SLAB>
+// at batch 4: 475 and 464 us). BLOCK (with SLAB): an item is a block of 32 channels of its tile's chunk, not all of
+// them. Also a kernel of its own: where the blocks are one, the loop over channels would cost 1 %.
+template <typename T, bool DET, bool SLAB, bool BLOCK>
 __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     __shared__ int s_geo[kGeo * kMaxLevels];
     __shared__ int s_start[kAccWaves][kRunKeys + 1];
@@ -1004,11 +1005,13 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
     // (2-4 us off the backward against dealing items x, x + 8, ...). Each counter has a 256-byte line of its
     // own: all waves taking items from one counter (or from counters sharing a line) serialize on
     // it, which cost the fold a quarter of its time. A wave whose queue has drained helps the others.
-    const int ch_blocks = SLAB ? p.ch_blocks : 1;
+    const int ch_blocks = BLOCK ? p.ch_blocks : 1;
     int total = SLAB ? *p.scan_done : p.tile_chunks[p.n_tiles];
     total = (total < 0 ? 0 : (total > p.max_items ? p.max_items : total)) * ch_blocks;
-    // With SLAB there are a few items per wave at most, and the waves take every nwaves-th one: a
-    // queue's atomics, and the visits to the drained queues at the end, would take longer than the sums.
+    // With SLAB the waves take every nwaves-th item: mostly there are a few for each, and a queue's atomics, and the
+    // visits to the drained queues at the end, would take longer than the sums. With many tiles it may be tens, most
+    // of them without a record, and what binning in one launch saves is still more than the queues would (85 for
+    // each wave, 128 slabs of five Swin maps, 300 queries of 20 samples: backward 590 us, 694 by the other passes).
     const int nwaves = gridDim.x * kAccWaves;
     int owner = SLAB ? 0 : blockIdx.x & (kQueues - 1), visited = SLAB ? kQueues - 1 : 0;
     auto qbase = [&](int q) { return SLAB ? 0 : (int)(((int64_t)total * q) / kQueues); };
@@ -1225,9 +1228,9 @@ __global__ __launch_bounds__(256, 2) void fold_runs_kernel(Params p) {
         const int lo = (C * grp) / kGroups, hi = (C * (grp + 1)) / kGroups;
         const int span = (C + kGroups - 1) / kGroups;
         const int key_lo = !by_units && hi > lo ? skey[lo] : 0;  // key of the slice's first record
-        // every channel, or with SLAB the item's block of them
-        const int ch_first = SLAB ? item % ch_blocks * (4 * kPixQ) : 0;
-        const int ch_end = SLAB ? min(ch_first + 4 * kPixQ, D) : D;
+        // every channel, or with BLOCK the item's block of them
+        const int ch_first = BLOCK ? item % ch_blocks * (4 * kPixQ) : 0;
+        const int ch_end = BLOCK ? min(ch_first + 4 * kPixQ, D) : D;
         for (int ch0 = ch_first; ch0 < ch_end; ch0 += 4 * kPixQ) {
             // the lane's first channel, or past the end of every row; channels past D in its other float4s may
             // read the next row's, and their sums are never stored
@@ -1470,17 +1473,28 @@ bool prefer_atomic(const Params& p) {
 }
 
 namespace {
-// Work items of a problem binned by bin_slab_kernel: the blocks of 32 channels are items of their own,
+// Work items of a problem binned by bin_slab_kernel: each block of 32 channels is an item of its own,
 // and a tile is cut into as few records per item (at least 64) as leaves every item a wave of the
 // fold's resident grid: an item's latency, not the sums, is what such a fold takes (64 thousand
 // samples of 64 channels: 42 us with items of 512 records and all channels, 17 us so).
+// Tiles that are more than eight times the waves by themselves, or four times with fewer than 32 records each, are
+// items of all channels: a block of a tile reads, ranks and sorts the tile's records once more, and stores 128 bytes
+// of each row. Backward us with blocks / all channels / the other passes, 8 heads over the DETR maps (fp32, fp16):
+//   19840 tiles: 19 records each, 96 channels 287 275 / 241 230 / 263 257, 256 channels 708 665 / 597 497 / 611 476;
+//                129 records, 96 channels 679 587 / 656 560 / 668 556
+//   9920 tiles:  19 records, 64 channels 120 116 / 112 106 / 147 150, 256 channels 356 344 / 305 281 / 348 334;
+//                65 records, 256 channels 557 484 / 585 477 / 706 594
+//   4960 tiles:  19 records, 128 channels 118 115 / 114 108 / 156 160; 65 records, 158 158 / 171 172 / 291 278
+//   2480 tiles:  19 records, 256 channels 118 112 / 143 135 / -
 constexpr int64_t kResidentWaves = 2048;
 void pick_small_items(Params& p) {
     const int64_t records = (int64_t)p.n_batch * p.Lq * p.M * p.K * 5 / 4;
     const int64_t tiles = (int64_t)p.n_batch * p.M * p.tiles_per_slab;
-    p.ch_blocks = (p.D + 4 * kPixQ - 1) / (4 * kPixQ);
+    const int blocks = (p.D + 4 * kPixQ - 1) / (4 * kPixQ);
+    const bool whole = tiles > 8 * kResidentWaves || (tiles > 4 * kResidentWaves && records < 32 * tiles);
+    p.ch_blocks = blocks > 1 && whole ? 0 : blocks;
     int r = 64;
-    while (r < kChunkRecords && (tiles + records / r) * p.ch_blocks > kResidentWaves) r *= 2;
+    while (r < kChunkRecords && (tiles + records / r) * (p.ch_blocks ? p.ch_blocks : 1) > kResidentWaves) r *= 2;
     p.item_records = r;
 }
 }  // namespace
@@ -1587,7 +1601,7 @@ bool plan_binned(Params& p) {
     const int64_t n_bins = n_slabs * bbase;
     const int64_t n_samples = (int64_t)p.n_batch * p.Lq * p.M * p.K;
     p.item_records = kChunkRecords;
-    p.ch_blocks = 1;
+    p.ch_blocks = 0;
     p.slab_bins = runs && slab_bins_apply(p);
     if (n_tiles > kSlabMaxTiles) p.slab_bins = 0;
     if (p.slab_bins) pick_small_items(p);
@@ -1705,14 +1719,17 @@ hipError_t launch_fold_runs(const Params& p, msda_dtype_t dtype, hipStream_t str
     if (grid <= 0) return hipErrorInvalidConfiguration;
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, p); };
     if (p.deterministic) {
-        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, true, false>);
-        else go(fold_runs_kernel<float, true, false>);
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, true, false, false>);
+        else go(fold_runs_kernel<float, true, false, false>);
+    } else if (p.slab_bins && p.ch_blocks > 0) {
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false, true, true>);
+        else go(fold_runs_kernel<float, false, true, true>);
     } else if (p.slab_bins) {
-        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false, true>);
-        else go(fold_runs_kernel<float, false, true>);
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false, true, false>);
+        else go(fold_runs_kernel<float, false, true, false>);
     } else {
-        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false, false>);
-        else go(fold_runs_kernel<float, false, false>);
+        if (dtype == MSDA_F16) go(fold_runs_kernel<_Float16, false, false, false>);
+        else go(fold_runs_kernel<float, false, false, false>);
     }
     return hipGetLastError();
 }

@@ -156,7 +156,7 @@ struct Params {
     int one_launch;             // the whole batch is in this launch
     int slab_bins;              // binning in one launch, a workgroup per (slab, level)
     int item_records;           // visible records of a tile per work item
-    int ch_blocks;              // work items per descriptor: blocks of 32 channels (1: an item takes all of them)
+    int ch_blocks;              // with slab_bins: work items per descriptor, blocks of 32 channels (0: one, of all)
     int max_items;              // capacity of `items`
     int scan_blocks;            // ceil(n_tiles / kScanTiles)
     int deterministic;          // grad_value summed in an order fixed by the inputs (bitwise reproducible)

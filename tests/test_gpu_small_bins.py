@@ -18,9 +18,14 @@ CASES = [
     (1, 1, 4, tuple((k + 1, 16 - k) for k in range(16)), 2, 700, "f32"),
     (3, 5, 48, ((31, 23), (16, 12), (8, 6)), 3, 999, "f16"),
     (1, 1, 32, ((120, 200),), 4, 4000, "f32"),                  # 375 tiles, few samples each
-    # 69632 one-pixel tiles in two blocks of channels: 68 work items for each of 2048 waves, the last four past
-    # the words that a wave holds ahead
-    (544, 8, 36, ((1, 1),) * 16, 1, 2, "f32"),
+    # more than 64 work items for each of 2048 waves, the last ones past the words that a wave holds ahead:
+    # 139264 one-pixel tiles with all channels (their second 32 are a remainder of 4), and 8192 tiles in 17 blocks
+    (1088, 8, 36, ((1, 1),) * 16, 1, 2, "f32"),
+    (64, 8, 516, ((1, 1),) * 16, 1, 2, "f16"),
+    # more than 8192 tiles of few records: all channels
+    (18, 8, 68, ((9, 9),) * 16, 1, 20, "f16"),
+    # and of more than 32 records: blocks of channels
+    (18, 8, 40, ((9, 9),) * 16, 1, 140, "f32"),
 ]
 
 
