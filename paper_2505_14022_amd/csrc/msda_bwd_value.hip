@@ -252,7 +252,7 @@ __device__ __forceinline__ void tile_totals(const Params& p, const int* g, int t
 #pragma unroll
     for (int i = 0; i < kKeyedBins; ++i) own += c[i];
     const int vis = own + e[0] + e[1] + e[2] + e[3] + e[4];
-    items = vis > 0 ? (vis + p.item_records - 1) / p.item_records : 1;
+    items = vis > 0 ? (vis + kChunkRecords - 1) / kChunkRecords : 1;
 }
 
 // Exclusive block scan of two sequences (256 threads); returns the block totals.
@@ -397,8 +397,8 @@ __device__ __forceinline__ void prep_tile(const Params& p, const int* s_geo, int
     const int nvis = na + nb + nc + nd;
     for (int c = lane; c < nit && first + c < p.max_items; c += 64) {
         int4* d = reinterpret_cast<int4*>(p.item_desc) + (size_t)(first + c) * 4;
-        const int beg = c * p.item_records;
-        d[0] = make_int4(beg, min(beg + p.item_records, nvis), nit > 1, l);
+        const int beg = c * kChunkRecords;
+        d[0] = make_int4(beg, min(beg + kChunkRecords, nvis), nit > 1, l);
         d[1] = make_int4(n, m, h_org, w_org);
         d[2] = make_int4(a0, na, b0, nb);
         d[3] = make_int4(c0, nc, d0, 0);

@@ -155,7 +155,7 @@ struct Params {
     int n_samples;              // n_batch * Lq * M * K
     int one_launch;             // the whole batch is in this launch
     int slab_bins;              // binning in one launch, a workgroup per (slab, level)
-    int item_records;           // visible records of a tile per work item
+    int item_records;           // with slab_bins: visible records of a tile per work item (kChunkRecords else)
     int ch_blocks;              // with slab_bins: work items per descriptor, blocks of 32 channels (0: one, of all)
     int max_items;              // capacity of `items`
     int scan_blocks;            // ceil(n_tiles / kScanTiles)
