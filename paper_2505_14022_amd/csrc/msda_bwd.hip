@@ -57,9 +57,9 @@ __device__ __forceinline__ void store_corner_sums(float (&G)[4], int sub, int4* 
 
 // Waves per SIMD that bwd_kernel may hold: seven with fp16 rows, although its registers allow eight. Beside it, on
 // the other stream, the counting pass waits for room with a slab's histogram in LDS (22 KB at the
-// Swin-feature shape), and eight waves of it left none until it had finished: the pass took 300 us of the
-// backward instead of 112, the step 981 us instead of 952. With fp32 rows eight are as fast or faster
-// (DETR-encoder step 395 us, 398 with seven).
+// Swin-feature shape), and eight waves of it leave little: step at that shape 962 us, 947 with seven (981 and 952
+// when a workgroup took a unit of LDS more). With fp32 rows eight are as fast or faster (DETR-encoder step 395 us,
+// 398 with seven).
 template <typename T, bool ATOMIC>
 constexpr int kBwdWaves = sizeof(T) == 2 && !ATOMIC ? 7 : 8;
 
@@ -75,7 +75,6 @@ void bwd_kernel(Params p) {
     // after all sums are formed
     __shared__ float s_g[kWaves][ATOMIC ? kAtomicRowFloats : 1];
     __shared__ int4 s_sum_atomic[kWaves][ATOMIC ? kMaxItems : 1];
-    __shared__ int s_q[kWaves][PPW];  // the wave's queries
     int4* const s_sum = ATOMIC ? &s_sum_atomic[0][0] : &s_off[0][0];  // [kWaves][kMaxItems] when used
     load_levels(p, s_lvl);
     if (p.reset && blockIdx.x == 0 && threadIdx.x == 0) *p.reset = 0;
@@ -89,9 +88,15 @@ void bwd_kernel(Params p) {
     const rsrc_t vr = make_rsrc(p.value, p.value_bytes);
     const rsrc_t gr = make_rsrc(p.grad_value, p.gv_bytes);
     const T* gout = static_cast<const T*>(p.grad_out);
-    if (lane < PPW) s_q[wave][lane] = query_at(p, s_lvl, t.q0 + lane);
-    wave_lds_sync();
-    const int q_mine = s_q[wave][ps];
+    // The wave's queries, one per lane, read by shuffles (lanes 0 to PPW - 1 are active wherever any lane is: every pass
+    // over the wave's items takes a multiple of PPW of them). Parked in LDS beside the items they cost each
+    // workgroup one more unit of 1280 bytes, and nine one-wave workgroups on a CU then left the binning passes of the
+    // other stream no room until bwd_kernel had finished: backward of one image, 6884 queries of 20 samples, 8 heads of 24
+    // fp16 channels 131 us, 121 so; deterministic, 3000 queries over the DETR maps, fp32 163.6 and 157.3.
+    static_assert(3 * kMaxLevels * 4 + kWaves * kMaxItems * 32 <= 13 * 1280, "LDS of bwd_kernel (not ATOMIC)");
+    const int q_lane = query_at(p, s_lvl, t.q0 + (lane & (PPW - 1)));
+    auto query = [&](int slot) { return __shfl(q_lane, slot, 64); };
+    const int q_mine = query(ps);
     const bool q_ok = q_mine < p.Lq;
     const size_t gout_row = ((size_t)(t.n * p.Lq + (q_ok ? q_mine : 0)) * p.M + t.m) * p.D;
     // when the query's channels fit one pass of its lanes, its grad_out row is read once here
@@ -123,7 +128,7 @@ void bwd_kernel(Params p) {
         for (int j = lane; j < PPW * kn; j += 64) {
             const int jq = small_div(j, inv_kn), jk = j - jq * kn;
             SampleDesc sd;
-            describe(p, s_lvl, t.n, t.m, s_q[wave][jq], k0 + jk, false, sd);
+            describe(p, s_lvl, t.n, t.m, query(jq), k0 + jk, false, sd);
             s_off[wave][j] = sd.off;
             s_x[wave][j] = make_float4(sd.a, sd.lh, sd.lw, 0.f);
         }
@@ -277,7 +282,7 @@ void bwd_kernel(Params p) {
         // differences of the G_c, scaled by the attention weight and the level size
         for (int j = lane; j < PPW * kn; j += 64) {
             const int jq = small_div(j, inv_kn), jk = j - jq * kn;
-            const int q = s_q[wave][jq];
+            const int q = query(jq);
             if (q < p.Lq) {
                 const int4 gi = s_sum[wave * kMaxItems + j];
                 const float G0 = __builtin_bit_cast(float, gi.x), G1 = __builtin_bit_cast(float, gi.y);
@@ -315,7 +320,7 @@ void bwd_kernel(Params p) {
             wave_lds_sync();
             for (int j = lane; j < PPW * kn; j += 64) {
                 const int jq = small_div(j, inv_kn), jk = j - jq * kn;
-                const int q = s_q[wave][jq];
+                const int q = query(jq);
                 if (q < p.Lq) {
                     float dot = 0.f;
                     for (int i = 0; i < kn; ++i) dot += s_x[wave][jq * kn + i].z;
