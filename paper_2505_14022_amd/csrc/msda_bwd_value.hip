@@ -1467,9 +1467,15 @@ bool prefer_atomic(const Params& p) {
     // run at 20.5 G pieces of 64 bytes a second. Backward us on atomics against binned, 8 heads of 32 channels, 300
     // queries of 16 samples over 17 821 pixels: batch 2 48 / 57, 3 65 / 67, 4 81 / 79, 8 147 / 125; 100
     // queries at batch 8 77 / 97; 16 channels at batch 8 86 / 117.
+    // Rows of a power of two channels take the atomics of whole lines, and binning has to save a fifth of them to be
+    // chosen: nearer the line, of 1000 problems of the ranges that models have, 14 were up to 27 % slower binned
+    // (1 image, 3493 queries of 4 samples over 208x209, 8 heads of 32: 64 / 82; 116 queries of 10, batch 6, 8 heads
+    // of 128 fp16 channels 85 / 99; 1956 queries of 6, 8 heads of 32 fp16 channels over 119x195 to 29x49 46 / 51),
+    // one by 5 % so. Other rows have slower atomics than this says, and none of them was slower binned.
     const double atomic_ns = 4.0 * samples * ((p.D + 15) / 16) / 20.5;
     const double rows = (double)p.n_batch * p.S * p.M * ((p.D + 31) / 32);
-    return atomic_ns < 20000.0 + 0.06 * rows;
+    const bool whole_lines = (p.D & (p.D - 1)) == 0;
+    return (whole_lines ? 0.8 : 1.0) * atomic_ns < 20000.0 + 0.06 * rows;
 }
 
 namespace {
