@@ -78,8 +78,13 @@ GatherLaunch plan_gather(Params& p, int ppw, int elem_bytes) {
     // Swin-feature shape fp16 188 / 853 -> 151 / 811, BEV-temporal fp16 207 / 792 -> 186 / 751,
     // DETR-encoder fp32 91 / 300 -> 89 / 293 (its 128-byte rows hit the cache more often, and its
     // loads run at 0.7 of the cache's rate). Strips of 16 rows were 2-5 % slower, of 4 rows 1-15 %
-    // in the backward; workgroups of 8 or 16 waves were slower.
-    p.strips = waves > 1 && p.Lq == p.S && p.S < kStripMaxPixels;
+    // in the backward; workgroups of 8 or 16 waves were slower. Not for rows longer than a line, which gain as
+    // much as the order costs (fp32 forward us with strips and without: 40 channels, 6 samples 85.6 / 82.6; 48
+    // channels, 16 samples 29.9 / 28.9; 64 channels, 24 samples 34.2 / 33.6), nor for queries of fewer samples (48 channels,
+    // 1 sample 59.2 / 54.5; 32 channels, 2 samples 22.9 / 21.9; fp16, 32 channels, 1 sample 13.4 / 12.5), against
+    // fp16 of 16 channels, 4 samples 103.1 / 122.7 and 32 channels, 8 samples 48.0 / 52.8.
+    p.strips = waves > 1 && p.Lq == p.S && p.S < kStripMaxPixels && p.D * elem_bytes <= kStripMaxRowBytes &&
+               p.K >= kStripMinSamples;
     for (int l = 0; l < p.L; ++l)
         if (p.H[l] > kStripMaxRows) p.strips = 0;
     p.head_group = waves > 1 && p.M % 2 == 0 && p.D * elem_bytes == 64 ? 2 : 1;

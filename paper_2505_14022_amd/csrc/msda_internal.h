@@ -63,6 +63,8 @@ constexpr int kCountQueries = 16 * kBinBlock;
 constexpr int kStripRows = 8;        // rows of a strip of the gather kernels' query order
 constexpr int64_t kStripMaxPixels = int64_t(1) << 20;  // maps of this many pixels, or of more than
 constexpr int kStripMaxRows = 1 << 17;                 // this many rows, keep the index order (small_div)
+constexpr int kStripMaxRowBytes = 128;  // as do calls of longer value rows,
+constexpr int kStripMinSamples = 4;     // or of fewer samples per query and head
 constexpr int kScanTiles = 256;      // tiles per workgroup in the scan passes (one per thread)
 constexpr int kAtomicMaxSamples = 16384;  // problems this small take the atomic grad_value path
 // Bytes of the static device scratch of msda_backward_noalloc (per GPU, held until the process ends).

@@ -36,7 +36,8 @@ void check(const Case& c, int ppw, int k_split_max) {
     p.Lq = c.Lq ? c.Lq : p.S;
     const msda::GatherLaunch g = msda::plan_gather(p, ppw, c.elem);
     // the query order and the head pairs do not depend on the arrangement
-    const bool pairs = g.waves > 1 && c.M % 2 == 0 && c.D * c.elem == 64, strips = g.waves > 1 && p.Lq == p.S;
+    const bool pairs = g.waves > 1 && c.M % 2 == 0 && c.D * c.elem == 64;
+    const bool strips = g.waves > 1 && p.Lq == p.S && c.D * c.elem <= 128 && p.K >= 4;
     if ((p.head_group == 2) != pairs || (p.strips != 0) != strips) {
         ++failures;
         std::printf("%s: strips %d, head group %d\n", c.name, p.strips, p.head_group);
@@ -72,6 +73,8 @@ int main() {
         {"pairs, odd batch", 3, 8, 32, 2, 4, {120, 120}, 0},
         {"pairs, cross-attention", 3, 6, 16, 4, 4, {100, 100, 50, 50}, 4500},
         {"odd heads", 2, 5, 32, 2, 3, {90, 70, 45, 35}, 0},
+        {"long rows", 2, 5, 36, 4, 3, {90, 70, 45, 35}, 0},
+        {"few samples", 2, 8, 32, 4, 3, {150, 90}, 0},
         {"wide rows", 2, 8, 32, 4, 4, {100, 150, 50, 75, 25, 38, 13, 19}, 0},
         {"cross-attention", 2, 8, 32, 4, 8, {116, 200, 58, 100}, 10000},
         {"decoder", 2, 8, 32, 4, 4, {100, 150, 50, 75, 25, 38, 13, 19}, 300},

@@ -14,7 +14,8 @@ code launches it and as each lane forms its addresses:
     the chunks whose first query lies in the x-th eighth of the rows of its level);
   * two heads per four-wave workgroup where two heads' rows of a pixel are one 128-byte line (half of
     the waves each, on the same queries), and the query order of self-attention over the maps (as
-    many queries as value pixels, four-wave workgroups): within each eighth of a level's rows, strips of
+    many queries as value pixels, four-wave workgroups, rows of at most 128 bytes and at least 4
+    samples): within each eighth of a level's rows, strips of
     at most 8 rows, column by column;
   * the sample split of small grids: a query chunk's K samples divided over up to 8 consecutive
     work items (at least 4 samples each, at most 4096 waves in all);
@@ -46,7 +47,9 @@ K_SPLIT_MIN_SAMPLES = 4  # ... keeping at least this many samples per part ...
 K_SPLIT_WAVES = 4096     # ... while the grid stays within this many waves
 STRIP_ROWS = 8           # most rows of a strip of the query order ...
 STRIP_MAX_PIXELS = 1 << 20  # ... which maps of this many pixels ...
-STRIP_MAX_ROWS = 1 << 17    # ... or of more rows than this do not take
+STRIP_MAX_ROWS = 1 << 17    # ... or of more rows than this do not take, ...
+STRIP_MAX_ROW_BYTES = 128   # ... nor calls of longer value rows ...
+STRIP_MIN_SAMPLES = 4       # ... or of fewer samples per query and head
 U32 = 1 << 32
 
 
@@ -176,7 +179,8 @@ def launches(N, S, M, D, Lq, L, P, es, shapes=None):
         ln = Launch(n0, cnt, vec, lpp, ppw, waves, qpb, chunks, num_blocks, grid, split, ks, hg)
         if Lq == S and shapes is None:
             raise ValueError("self-attention over the maps needs the level shapes")
-        if waves > 1 and Lq == S and S < STRIP_MAX_PIXELS and all(h <= STRIP_MAX_ROWS for h, _ in shapes):
+        if (waves > 1 and Lq == S and S < STRIP_MAX_PIXELS and all(h <= STRIP_MAX_ROWS for h, _ in shapes) and
+                D * es <= STRIP_MAX_ROW_BYTES and L * P >= STRIP_MIN_SAMPLES):
             ln.order = strip_order(shapes)
         if split and ks == 1 and Lq == S:
             bc, count, cap = band_table(shapes, qpb)

@@ -38,7 +38,7 @@ BANDS = [
 # four-wave workgroups of two heads each (64-byte rows): in the query order of bands of rows, in query eighths and
 # in slab ranges
 PAIRS = [
-    (2, 8, 32, ((56, 60), (28, 30), (5, 9)), 1, 56 * 60 + 28 * 30 + 5 * 9, "f16"),
+    (2, 8, 32, ((56, 60), (28, 30), (5, 9)), 2, 56 * 60 + 28 * 30 + 5 * 9, "f16"),
     (2, 8, 16, ((90, 91),), 2, 5001, "f32"),
     (3, 6, 32, ((90, 91),), 2, 4001, "f16"),
 ]
