@@ -1,8 +1,8 @@
 // MSDA backward, part 1 (paper Sec. 4.2): gradients w.r.t. the sampling locations and the
 // attention weights, for gfx950 (CDNA4, wave64).
 //
-// Same mapping as the forward kernel (one (batch, head) slab and a run of queries per workgroup,
-// LPP lanes per query, per-sample descriptions parked in LDS). For each sample every lane forms
+// Same mapping as the forward kernel (one or two heads of a batch item and a run of the query order per
+// workgroup, LPP lanes per query, per-sample descriptions parked in LDS). For each sample every lane forms
 // its channels' share of the four corner dot products G_c = <g, v_c> from the gathered corner rows
 // (the rows of several samples are in flight at once); the shares are summed over the query's
 // lanes with DPP row operations, and <g, s>, <g, ds/dw_im>, <g, ds/dh_im> follow from the four

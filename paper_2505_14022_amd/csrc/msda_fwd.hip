@@ -2,10 +2,11 @@
 // attention-weighted bilinear samples (paper Sec. 3-4.1).
 //
 // Mapping:
-//   * A workgroup of 256 lanes owns one (batch n, head m) pair and a run of consecutive queries,
-//     so every value row it touches lies in that head's slab. Workgroups are renumbered so that
-//     all the work of one (n, m) slab lands on one XCD (consecutive workgroup ids are dealt
-//     round-robin to the 8 XCDs): the slab's value lines stay in one XCD's L2.
+//   * A workgroup of 256 lanes (64 in small grids) owns one (batch n, head m) pair and a run of queries, or, where
+//     two heads' rows of a pixel are one cache line, two heads and half as many queries. Consecutive places of
+//     the query order are consecutive queries, or with self-attention over the maps a patch of a level (query_at).
+//     Workgroups are renumbered so that an XCD reads few slabs, or a band of rows of each (block_work;
+//     consecutive workgroup ids are dealt round-robin to the 8 XCDs): its value lines stay in the XCD's L2.
 //   * Within a wave, LPP lanes serve one query; each lane owns VEC contiguous channels, so one
 //     corner of one sample is a single coalesced row read (D=32 fp32: 8 lanes x 16 B = 128 B).
 //     A wave serves 64/LPP queries at once.
