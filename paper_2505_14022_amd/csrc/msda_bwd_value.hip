@@ -1610,11 +1610,6 @@ bool plan_binned(Params& p) {
     p.ch_blocks = 0;
     p.slab_bins = runs && slab_bins_apply(p);
     if (n_tiles > kSlabMaxTiles) p.slab_bins = 0;
-    // Full workgroups (more than 12 of their 16 samples per thread, 48 us) and nearly 2 M samples: the other passes hide
-    // as much behind bwd_kernel. Fused step of 5104 queries of 12 samples, 8 heads of 24 fp32 channels at batch 4, 250 us
-    // slab by slab and 238; backward of 14 971 queries of 4, 30 slabs of 128 channels 487 and 483; below 1.5 M
-    // samples slab by slab was 2 to 35 % faster.
-    if (!atomics_suffice(p) && p.Lq * p.P > 12 * kSlabThreads && n_samples > 1500000) p.slab_bins = 0;
     if (p.slab_bins) pick_small_items(p);
     const int64_t max_items = 2 * n_tiles + 4 * n_samples / p.item_records + 1;
     if (n_bins + 1 > kMaxIndex || max_items > kMaxIndex || n_samples > kMaxIndex) return false;
