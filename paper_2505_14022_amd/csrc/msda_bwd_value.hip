@@ -1485,7 +1485,9 @@ namespace {
 // samples of 64 channels: 42 us with items of 512 records and all channels, 17 us so).
 // Tiles that are more than eight times the waves by themselves, or four times with fewer than 32 records each, are
 // items of all channels: a block of a tile reads, ranks and sorts the tile's records once more, and stores 128 bytes
-// of each row. Backward us with blocks / all channels / the other passes, 8 heads over the DETR maps (fp32, fp16):
+// of each row. Only where a row is whole 64-byte pieces: of others, the two passes over an item's channels write the pieces
+// that they share in part, far apart (8 heads over the DETR maps at batch 8, 300 queries, fp32, blocks / all channels: 40
+// channels 205 / 239, 52 channels 262 / 300, 48 channels 199 / 175). Backward us with blocks / all channels / the other passes, 8 heads over the DETR maps (fp32, fp16):
 //   19840 tiles: 19 records each, 96 channels 287 275 / 241 230 / 263 257, 256 channels 708 665 / 597 497 / 611 476;
 //                129 records, 96 channels 679 587 / 656 560 / 668 556
 //   9920 tiles:  19 records, 64 channels 120 116 / 112 106 / 147 150, 256 channels 356 344 / 305 281 / 348 334;
@@ -1497,7 +1499,7 @@ void pick_small_items(Params& p) {
     const int64_t records = (int64_t)p.n_batch * p.Lq * p.M * p.K * 5 / 4;
     const int64_t tiles = (int64_t)p.n_batch * p.M * p.tiles_per_slab;
     const int blocks = (p.D + 4 * kPixQ - 1) / (4 * kPixQ);
-    const bool whole = tiles > 8 * kResidentWaves || (tiles > 4 * kResidentWaves && records < 32 * tiles);
+    const bool whole = p.D % 16 == 0 && (tiles > 8 * kResidentWaves || (tiles > 4 * kResidentWaves && records < 32 * tiles));
     p.ch_blocks = blocks > 1 && whole ? 0 : blocks;
     int r = 64;
     while (r < kChunkRecords && (tiles + records / r) * (p.ch_blocks ? p.ch_blocks : 1) > kResidentWaves) r *= 2;

@@ -19,11 +19,13 @@ CASES = [
     (3, 5, 48, ((31, 23), (16, 12), (8, 6)), 3, 999, "f16"),
     (1, 1, 32, ((120, 200),), 4, 4000, "f32"),                  # 375 tiles, few samples each
     # more than 64 work items for each of 2048 waves, the last ones past the words that a wave holds ahead:
-    # 139264 one-pixel tiles with all channels (their second 32 are a remainder of 4), and 8192 tiles in 17 blocks
-    (1088, 8, 36, ((1, 1),) * 16, 1, 2, "f32"),
+    # 139264 one-pixel tiles with all channels (their second 32 are a remainder of 16), and 8192 tiles in 17 blocks
+    (1088, 8, 48, ((1, 1),) * 16, 1, 2, "f32"),
     (64, 8, 516, ((1, 1),) * 16, 1, 2, "f16"),
     # more than 8192 tiles of few records: all channels
-    (18, 8, 68, ((9, 9),) * 16, 1, 20, "f16"),
+    (18, 8, 80, ((9, 9),) * 16, 1, 20, "f16"),
+    # the same of rows that are no whole 64-byte pieces: blocks
+    (18, 8, 68, ((9, 9),) * 16, 1, 20, "f32"),
     # and of more than 32 records: blocks of channels
     (18, 8, 40, ((9, 9),) * 16, 1, 140, "f32"),
 ]
